@@ -148,10 +148,17 @@ struct WinSetup {
 // min / max alone.  One thread adds at most `per_thread` values.  For integer
 // sources its sums of W * q stay exact integers below 2^53 when max|W| *
 // max|q| * per_thread < 2^53, and a tensor beyond that bound goes to the exact
-// general pass.  fp32 values (W up to 2^52) always use the split form
-// W = Wh * 2^26 + Wl, exact while 2^26 * max|q| * per_thread < 2^53, which
-// the launcher's bound on per_thread guarantees.
-template <int KIND>
+// general pass.  Split sources (fp32, and int64 values, whose scale leaves
+// most of them beyond that bound) use the form W = Wh * 2^26 + Wl, exact while
+// 2^26 * max|q| * per_thread < 2^53, which the launcher's bound on per_thread
+// guarantees (51.4 M int64 values of a 16-bit first layer: 13.3 ms in the
+// general pass's 128-bit errors, 0.16 ms in the split window); int64 values beyond the unsplit bound still have to lie within
+// the general pass's range, whose error they raise otherwise.
+constexpr bool win_split(int kind, int dt) {
+  return kind == FXPQ_SRC_F32 || (kind == FXPQ_SRC_INT && dt == FXPQ_I64);
+}
+
+template <int KIND, bool SPLIT = KIND == FXPQ_SRC_F32>
 __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, int sign_req,
                                      int fl_lo, int fl_hi, int mode, int64_t per_thread) {
   WinSetup w;
@@ -162,7 +169,9 @@ __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, 
   if (!w.u.ok) w.verdict = 3;
   else if (mode == MODE_REPORT || wl > 16 || wl == 1 || wmax >= kTwo52) w.verdict = 2;
   else if (w.u.beta_nosat >= fl_hi) w.verdict = 1;
-  else if (KIND != FXPQ_SRC_F32 && wmax * qabs * (double)per_thread >= kTwo53) w.verdict = 2;
+  else if (KIND != FXPQ_SRC_F32 && wmax * qabs * (double)per_thread >= kTwo53 &&
+           (!SPLIT || ldexp(w.u.absmax, imax(fl_hi - w.u.sv, 0)) >= 0x1p62))
+    w.verdict = 2;
   w.b0 = imax(fl_lo, w.u.beta_nosat);
   w.b1 = (w.b0 + kWindow - 1 < fl_hi) ? w.b0 + kWindow - 1 : fl_hi;
   w.nc = w.b1 - w.b0 + 1;

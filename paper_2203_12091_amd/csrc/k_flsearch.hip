@@ -67,7 +67,7 @@ __device__ inline void win_loop(const SrcDev& s, int64_t n, const FlsU& u, const
   // to qmax + 1 (same error either way, but the code must be clamped).
   auto consume = [&](double W, int* cq) {
     double q[kWindow];
-    win_consume<KIND == FXPQ_SRC_F32, NONNEG, CLAMP0, NB>(wc, acc, W, q);
+    win_consume<win_split(KIND, DT), NONNEG, CLAMP0, NB>(wc, acc, W, q);
     if constexpr (CODES) {
 #pragma unroll
       for (int j = 0; j < kWindow; ++j) cq[j] = (int)q[j];
@@ -365,7 +365,8 @@ __global__ __launch_bounds__(kThreads) void k_fls_window(
     const double* mm, long long* part_i, double* part_f, FlsPlan* plan, fxpq_fmt* out,
     unsigned* flags, int8_t* y, int8_t* y_alt) {
   __shared__ WinShared wsh;
-  const WinSetup ws = win_setup<KIND>(s, mm, wl, sign_req, fl_lo, fl_hi, mode, per_thread);
+  const WinSetup ws =
+      win_setup<KIND, win_split(KIND, DT)>(s, mm, wl, sign_req, fl_lo, fl_hi, mode, per_thread);
   const FlsU& u = ws.u;
 
   // Decisions every block takes identically before touching the data.
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(kThreads) void k_fls_window(
     case 2: win_loop<KIND, DT, true, false, NB, CODES>(s, n, u, ws, wcd, acc); break;
     default: win_loop<KIND, DT, true, true, NB, CODES>(s, n, u, ws, wcd, acc); break;
   }
-  if constexpr (KIND == FXPQ_SRC_F32) win_write_partials(acc, NB, blockIdx.x, part_i, part_f, wsh);
+  if constexpr (win_split(KIND, DT)) win_write_partials(acc, NB, blockIdx.x, part_i, part_f, wsh);
   else win_write_partials_int(acc, NB, blockIdx.x, part_i, part_f, wsh);
 }
 
@@ -787,6 +788,178 @@ struct WinIn {
   double* cf;
 };
 
+// ---------------------------------------------------------------------------
+// The general pass over word lengths 2..16 and integers |W| < 2^52: per
+// candidate the exact sums of the window pass (sum q^2 and sum W q, W split as
+// Wh 2^26 + Wl), kGenGroup candidates per read of the values, the candidates
+// compared by 2^(2d) sum q^2 - 2^(d+1) sum W q (sum W^2 is common to all).
+// About 8 fp64 operations per value and candidate where the 128-bit errors
+// take ~70 instructions: bound by those operations, not by memory.  Measured
+// searches of 25.7 M values with one far outlier (10 to 14 candidates left),
+// 128-bit errors -> these sums: fp32 3519 -> 263 us at 8 bits, 4591 -> 345 us
+// at 4 bits; C-Block values 6064 -> 351 us at 8 bits.
+// ---------------------------------------------------------------------------
+constexpr int kGenGroup = 4;
+constexpr int kGenFlush = 512;  // values per thread between flushes (as kWinMaxPerThread)
+
+__device__ inline int gen_cand(const GenPlan& g, int j) {
+  return (g.extra != INT_MIN) ? (j == 0 ? g.extra : g.glo + j - 1) : g.glo + j;
+}
+__device__ inline int gen_count(const GenPlan& g) {
+  return g.ghi - g.glo + 1 + (g.extra != INT_MIN ? 1 : 0);
+}
+
+// Every block adds its share of the values: candidate j's block sums go to
+// part[(j * kGenChunks + block) * 3]: sum q^2, then sum W q in 128 bits.
+template <int KIND, int DT>
+__device__ void general_sums(const SrcDev& s, int64_t n, const FlsU& u, const GenPlan& g,
+                             unsigned long long* part) {
+  using PK = Pack<KIND, DT>;
+  __shared__ long long sh[4][kGenGroup][6];
+  const int nc = gen_count(g);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int j0 = 0; j0 < nc; j0 += kGenGroup) {
+    double cj[kGenGroup], A[kGenGroup], PH[kGenGroup], PL[kGenGroup];
+    long long Ai[kGenGroup], PHi[kGenGroup], PLi[kGenGroup];
+#pragma unroll
+    for (int k = 0; k < kGenGroup; ++k) {
+      cj[k] = ldexp(1.0, gen_cand(g, imax(0, (j0 + k < nc ? j0 + k : nc - 1))) - u.sigma);
+      A[k] = PH[k] = PL[k] = 0.0;
+      Ai[k] = PHi[k] = PLi[k] = 0;
+    }
+    auto add = [&](double W) {
+      const double Wh = floor(W * kTwoM26);
+      const double Wl = fma(-Wh, kTwo26, W);
+#pragma unroll
+      for (int k = 0; k < kGenGroup; ++k) {
+        const double q = max64(min64(rint(W * cj[k]), u.qmax), u.qmin);
+        A[k] = fma(q, q, A[k]);
+        PH[k] = fma(Wh, q, PH[k]);
+        PL[k] = fma(Wl, q, PL[k]);
+      }
+    };
+    auto flush = [&]() {
+#pragma unroll
+      for (int k = 0; k < kGenGroup; ++k) {
+        Ai[k] += exact_i64(A[k]);
+        PHi[k] += exact_i64(PH[k]);
+        PLi[k] += exact_i64(PL[k]);
+        A[k] = PH[k] = PL[k] = 0.0;
+      }
+    };
+    ThreadVals<PK::V> tv;
+    thread_vals_init<KIND, DT>(s, (int64_t)blockIdx.x * kThreads * PK::V, tv);
+    int cnt = 0;
+    auto count = [&](int values) {
+      cnt += values;
+      if (cnt > kGenFlush - PK::EP) {
+        flush();
+        cnt = 0;
+      }
+    };
+    bool packets = true;
+    if constexpr (KIND == FXPQ_SRC_ACC) packets = ((int64_t)gridDim.x * kThreads * PK::V) % s.channels == 0;
+    if (packets) {
+      stream_packets<KIND, DT, false, kWinSets>(s, n, tv, [&](const double* v, int64_t, int) {
+#pragma unroll
+        for (int e = 0; e < PK::EP; ++e) add(v[e] * u.wscale);
+        count(PK::EP);
+      });
+      if (blockIdx.x == 0 && threadIdx.x == 0)
+        for (int64_t i = n - n % PK::EP; i < n; ++i) add(load1<KIND, DT>(s, i) * u.wscale);
+    } else {
+      // a grid stride that does not keep the thread's channels
+      const int64_t stride = (int64_t)gridDim.x * kThreads;
+      for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
+        add(load1<KIND, DT>(s, i) * u.wscale);
+        count(1);
+      }
+    }
+    flush();
+#pragma unroll
+    for (int k = 0; k < kGenGroup; ++k) {
+      const long long q6[6] = {Ai[k] >> 32,  Ai[k] & 0xFFFFFFFFll,  PHi[k] >> 32,
+                               PHi[k] & 0xFFFFFFFFll, PLi[k] >> 32, PLi[k] & 0xFFFFFFFFll};
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        const long long t = wave_reduce(q6[i], OpAddL());
+        if (lane == 0) sh[wave][k][i] = t;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < kGenGroup && j0 + (int)threadIdx.x < nc) {
+      const int k = threadIdx.x;
+      auto tot = [&](int i) -> __int128 {
+        const long long hi = sh[0][k][i] + sh[1][k][i] + sh[2][k][i] + sh[3][k][i];
+        const long long lo = sh[0][k][i + 1] + sh[1][k][i + 1] + sh[2][k][i + 1] + sh[3][k][i + 1];
+        return (__int128)hi * ((__int128)1 << 32) + lo;
+      };
+      const __int128 P = tot(2) * (__int128)67108864 + tot(4);
+      unsigned long long* p = part + ((int64_t)(j0 + k) * kGenChunks + blockIdx.x) * 3;
+      p[0] = (unsigned long long)tot(0);
+      p[1] = (unsigned long long)P;
+      p[2] = (unsigned long long)(P >> 64);
+    }
+    __syncthreads();
+  }
+}
+
+// One block: each wave sums candidates over the blocks, one thread compares
+// them exactly, ties to the larger fl.
+__device__ void general_sums_decide(int wl, int sigma, const GenPlan& g,
+                                    const unsigned long long* part, fxpq_fmt* out) {
+  __shared__ unsigned long long tot[kMaxCand][4];  // sum q^2, sum W q (128 bits each)
+  const int nc = gen_count(g);
+  const int lane = threadIdx.x & 63;
+  for (int j = threadIdx.x >> 6; j < nc; j += kThreads / 64) {
+    long long ah = 0, al = 0, p0 = 0, p1 = 0, p2 = 0;
+    for (int b = lane; b < (int)gridDim.x; b += 64) {
+      const unsigned long long* p = part + ((int64_t)j * kGenChunks + b) * 3;
+      ah += (long long)(p[0] >> 32);
+      al += (long long)(p[0] & 0xFFFFFFFFull);
+      p0 += (long long)(p[1] & 0xFFFFFFFFull);
+      p1 += (long long)(p[1] >> 32);
+      p2 += (long long)p[2];
+    }
+    ah = wave_reduce(ah, OpAddL());
+    al = wave_reduce(al, OpAddL());
+    p0 = wave_reduce(p0, OpAddL());
+    p1 = wave_reduce(p1, OpAddL());
+    p2 = wave_reduce(p2, OpAddL());
+    if (lane == 0) {
+      const __int128 A = (__int128)ah * ((__int128)1 << 32) + al;
+      const __int128 P = (__int128)p2 * ((__int128)1 << 64) + (__int128)p1 * ((__int128)1 << 32) + p0;
+      tot[j][0] = (unsigned long long)A;
+      tot[j][1] = (unsigned long long)(A >> 64);
+      tot[j][2] = (unsigned long long)P;
+      tot[j][3] = (unsigned long long)(P >> 64);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  // every exponent non-negative by a common factor 2^off; a candidate whose
+  // codes are all zero has K = 0 (so d is at most ~54 where a shift counts)
+  const int dmin = sigma - g.ghi;
+  int off = 0;
+  if (2 * dmin < 0) off = -2 * dmin;
+  if (dmin + 1 + off < 0) off = -(dmin + 1);
+  Big best{};
+  int bfl = 0;
+  for (int j = 0; j < nc; ++j) {
+    const int fl = gen_cand(g, j), d = sigma - fl;
+    const __int128 A = (__int128)(((unsigned __int128)tot[j][1] << 64) | tot[j][0]);
+    const __int128 P = (__int128)(((unsigned __int128)tot[j][3] << 64) | tot[j][2]);
+    Big k{};
+    if (A != 0 || P != 0)
+      k = big_sub(big_shl(big_from_i128(A), 2 * d + off), big_shl(big_from_i128(P), d + 1 + off));
+    if (j == 0 || big_cmp(k, best) <= 0) {
+      best = k;
+      bfl = fl;
+    }
+  }
+  *out = fxpq_fmt{wl, bfl, g.sign, 0};
+}
+
 // Exact errors of the remaining candidates over (candidate, chunk) items; the
 // last block to finish sums the chunk partials and decides.  Nothing runs
 // unless the window pass left candidates undecided (and only then is the
@@ -802,7 +975,8 @@ __global__ __launch_bounds__(kThreads) void k_fls_general(
   if (wi.ci && blockIdx.x == 0) win_slots_clear(wi.ci, wi.cf);
   bool from_plan = true;
   if (wi.decide) {
-    const WinSetup ws = win_setup<KIND>(s, mm, wl, wi.sign_req, fl_lo, fl_hi, wi.mode, wi.per_thread);
+    const WinSetup ws = win_setup<KIND, win_split(KIND, DT)>(s, mm, wl, wi.sign_req, fl_lo, fl_hi,
+                                                             wi.mode, wi.per_thread);
     if (ws.verdict == 0) {  // else the window pass wrote the plan
       from_plan = false;
       if (threadIdx.x < 64) {
@@ -841,6 +1015,25 @@ __global__ __launch_bounds__(kThreads) void k_fls_general(
   }
   const long long qmax = (1ll << (wl - sign)) - 1;
   const long long qmin = sign ? -(1ll << (wl - 1)) : 0;
+  // Word lengths 2..16 with integers |W| < 2^52 (fp32: W = v 2^(fl_hi + 24)):
+  // the candidates' exact sums in fp64, four per read of the values.
+  const int sigf = (KIND == FXPQ_SRC_F32) ? sigma : sv;
+  if (wl >= 2 && wl <= 16 && !d_sse && absmax * ldexp(1.0, sigf - sv) < kTwo52) {
+    const FlsU u = fls_uniform<KIND>(s, mm, wl, sign, fl_lo, fl_hi);
+    // candidates below beta_nosat never win (see the top of this file)
+    const int lo = extra == INT_MIN ? imax(glo, u.beta_nosat < ghi ? u.beta_nosat : ghi) : glo;
+    const GenPlan gf{1, 0, sign, lo, ghi, extra};
+    general_sums<KIND, DT>(s, n, u, gf, part);
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(done, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    general_sums_decide(wl, u.sigma, gf, part, out);
+    if (threadIdx.x == 0) *done = 0u;  // ready for the next search
+    return;
+  }
   const int64_t clen = (n + nchunks - 1) / nchunks;
   // int64 values are scaled in integers (fp64 holds them exactly only below
   // 2^53); |v| 2^(sigma - sv) < 2^62 after the check above (a shift of 62 or
@@ -1010,7 +1203,20 @@ static hipError_t general_pass(const Ctx& c, const SrcDev& s, int64_t n, int wl,
   int nchunks = (int)((n + 65535) / 65536);
   if (nchunks > kGenChunks) nchunks = kGenChunks;
   if (nchunks < 1) nchunks = 1;
+  // about a block per CU; for C-Block values the grid stride is a multiple of
+  // the channels where at most kGenChunks blocks allow it
   int gblocks = 240;
+  if (s.kind == FXPQ_SRC_ACC) {
+    const int per = kThreads * 4;  // values per block and iteration
+    int a = s.channels, b = per;
+    while (b) {
+      const int t = a % b;
+      a = b;
+      b = t;
+    }
+    const int g = s.channels / a;
+    if (g <= kGenChunks) gblocks = g * imax(1, 240 / g);
+  }
   FXPQ_DISPATCH_SRC(s.kind, s.dtype,
                     (k_fls_general<K_, D_><<<gblocks, kThreads, 0, c.stream>>>(
                         s, n, wl, fl_lo, fl_hi, nchunks, d_minmax, wi, plan, c.sc.gen_part,

@@ -1,0 +1,81 @@
+"""The FL search's paths beyond its one-read window, against the CPU oracle:
+int64 values (split sums in the window) and the exact pass over the candidates
+above the window (fp64 sums of four candidates per read), at tensor sizes
+around a packet, a block and a flush, and for C-Block values whose channel
+count does / does not fit the pass's grid stride."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import DEV, dev, fmt_dev, fmt_host, fmt_new, note
+
+pytestmark = pytest.mark.gpu
+
+FL_LO, FL_HI = -8, 15
+
+
+@pytest.fixture(scope="module")
+def fx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2203_12091_amd import fxpq
+    return fxpq
+
+
+@pytest.fixture(scope="module")
+def h(fx):
+    import torch
+    hd = fx.Handle(0)
+    fx.set_stream(hd, torch.cuda.current_stream())
+    yield hd
+    hd.close()
+
+
+def values(seed, n, bits, heavy):
+    """Normal integers of about `bits` bits; heavy: a few outliers far above, so that short word lengths clip them."""
+    g = synth.rng_for(seed, "paths")
+    v = (g.standard_normal(n) * 2.0 ** (bits - (6 if heavy else 2))).astype(np.int64)
+    if heavy:
+        idx = g.choice(n, max(1, n // 5000), replace=False)
+        v[idx] = (2.0 ** (bits - 1) * (1 + g.random(idx.size))).astype(np.int64)
+    return np.clip(v, -(2 ** bits) + 1, 2 ** bits - 1)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 513, 131_075, 700_001])
+@pytest.mark.parametrize("bits,s", [(44, 30), (51, 41), (46, 20)])
+def test_int64_search(fx, h, orc, n, bits, s):
+    import torch
+    sd = torch.tensor([s], dtype=torch.int32, device=DEV)
+    for heavy in (False, True):
+        v = values(n + bits, n, bits, heavy)
+        vd = dev(v)
+        for wl in (2, 4, 8, 12, 16):
+            note("int64", n, bits, s, heavy, wl)
+            out = fmt_new()
+            fx.fl_search(h, fx.src_int(vd, fx.I64, sd), n, wl, fx.SIGN_AUTO, FL_LO, FL_HI, out)
+            ofl, osign, _ = orc.fl_search_i64(v, s, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+            assert fmt_host(out) == (wl, ofl, osign, 0), (heavy, wl)
+    assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("channels", [1, 7, 100, 1000, 1028])  # 1028: no grid of the pass keeps its channels
+def test_cblock_values_above_the_window(fx, h, orc, channels):
+    import torch
+    g = synth.rng_for(channels, "paths-acc")
+    rows = 300_007 // channels
+    acc = values(channels, rows * channels, 24, True).astype(np.int32).reshape(rows, channels)
+    a1 = g.integers(2 ** 14, 2 ** 15, channels).astype(np.int32)
+    ep = fx.epilogue(channels, 9, fmt_dev(8, 5, 1), scale=dev(a1), fl_scale=15)
+    v, s = orc.epilogue(acc.astype(np.int64), 14, a1=a1, fl_a1=15)
+    above = 0
+    for wl in (3, 5, 8, 16):
+        note("acc", channels, wl)
+        out = fmt_new()
+        fx.fl_search(h, fx.src_acc(dev(acc), ep), acc.size, wl, fx.SIGN_AUTO, FL_LO, FL_HI, out)
+        ofl, osign, _ = orc.fl_search_i64(np.ravel(v), s, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+        assert fmt_host(out) == (wl, ofl, osign, 0), wl
+        qmax = 2 ** (wl - osign) - 1
+        above += float(np.max(v)) * 2.0 ** (ofl - 1 - s) > qmax + 0.5  # best fl more than one above no saturation
+    assert above  # the fixture reaches the exact pass
+    assert fx.sync_status(h) == 0
