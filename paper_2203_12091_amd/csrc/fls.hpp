@@ -152,7 +152,7 @@ struct WinSetup {
 // most of them beyond that bound) use the form W = Wh * 2^26 + Wl, exact while
 // 2^26 * max|q| * per_thread < 2^53, which the launcher's bound on per_thread
 // guarantees (51.4 M int64 values of a 16-bit first layer: 13.3 ms in the
-// general pass's 128-bit errors, 0.16 ms in the split window); int64 values beyond the unsplit bound still have to lie within
+// general pass, see k_fls_general); beyond the unsplit bound they still have to lie within
 // the general pass's range, whose error they raise otherwise.
 constexpr bool win_split(int kind, int dt) {
   return kind == FXPQ_SRC_F32 || (kind == FXPQ_SRC_INT && dt == FXPQ_I64);
