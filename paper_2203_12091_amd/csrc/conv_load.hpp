@@ -37,9 +37,12 @@ __device__ inline int lds_off(int row, int chunk) {
 // three-stage LDS ring (global_load_lds), two slabs in flight.  HALO4 /
 // HALO8: C % 64 == 0, tiles of whole output-image rows whose input patch
 // (up to 256 / 512 pixels per channel chunk) is loaded into LDS once and read
-// by every filter tap, weights through the DMA ring.
+// by every filter tap, weights through the DMA ring.  SPLIT64, SPLIT32:
+// C % 64 == 0, 64 x 64 / 32 x 32 tiles whose depth the four waves split
+// (split_tile).
 enum Loader { LD_FAST64 = 0, LD_GEN16 = 1, LD_RGB4 = 2, LD_DMA64 = 3, LD_HALO4 = 4, LD_HALO8 = 5,
-              LD_RGB8 = 6 };
+              LD_RGB8 = 6, LD_SPLIT64 = 7, LD_SPLIT32 = 8 };
+constexpr int split_t(int loader) { return loader == LD_SPLIT64 ? 2 : (loader == LD_SPLIT32 ? 1 : 0); }
 
 constexpr bool is_halo(int loader) { return loader == LD_HALO4 || loader == LD_HALO8; }
 
@@ -125,15 +128,16 @@ struct ConvArgs {
 
 // Tile configurations: block BM x BN, four waves of (32 TM) x (32 TN), MINW
 // waves per SIMD requested from the register allocator.
-enum TileCfg { TC_256x64 = 0, TC_128x128 = 1, TC_256x128 = 2, TC_H224x256 = 3, TC_H128x256 = 4 };
+enum TileCfg { TC_256x64 = 0, TC_128x128 = 1, TC_256x128 = 2, TC_H224x256 = 3, TC_H128x256 = 4,
+               TC_64x64 = 5, TC_32x32 = 6 };
 
 // Accumulators per thread of a configuration (the per-thread bound of the
 // fused window epilogue).
 constexpr int conv_per_thread(int cfg) { return cfg == TC_256x128 ? 128 : 64; }
 
 // Slabs of a BM x BN tile, 64 bytes of depth each, loaded straight into an LDS
-// stage (C % 64 == 0): each wave fills 1 KB pieces (16 rows of 64 bytes), piece
-// q = 4 j + wave, lane l -> row 16 q + l / 4, physical chunk l % 4, which holds
+// stage (C % 64 == 0): each of WAVES waves fills 1 KB pieces (16 rows of 64
+// bytes), piece q = WAVES j + wave, lane l -> row 16 q + l / 4, physical chunk l % 4, which holds
 // logical chunk (l % 4) ^ f(row) of the swizzled layout.  The channel chunks
 // are walked outermost and the filter taps innermost.  The walk is incremental:
 // a scalar tap (ir, is) with its offsets, each row's address of tap (0, 0)
@@ -141,9 +145,9 @@ constexpr int conv_per_thread(int cfg) { return cfg == TC_256x128 ? 128 : 64; }
 // and 64-bit products of addressing every slab from its number took longer than
 // its MFMAs: 14x14x256 3x3 at batch 256 ran 56 -> 48 us plain, 74 -> 66 us
 // predicted).
-template <int BM, int BN>
+template <int BM, int BN, int WAVES = 4>
 struct RingLoad {
-  static constexpr int AJ = BM / 64, BJ = BN / 64;
+  static constexpr int AJ = BM / (16 * WAVES), BJ = BN / (16 * WAVES);
   static constexpr int kOps = AJ + BJ;  // loads per wave and slab
   int64_t arow[AJ];                     // address of (ih0, iw0, chunk), used where it is valid
   int aih[AJ], aiw[AJ];
@@ -156,7 +160,7 @@ struct RingLoad {
   __device__ inline void cols(const ConvArgs& a, int a_off, int n0, int wave, int lane) {
 #pragma unroll
     for (int j = 0; j < BJ; ++j) {
-      const int row = 16 * (4 * j + wave) + (lane >> 2);
+      const int row = 16 * (WAVES * j + wave) + (lane >> 2);
       const int col = n0 + row;
       const int cc = col < a.K ? col : a.K - 1;
       bsrc[j] = a.w + (int64_t)cc * a.wrow + (((lane & 3) ^ lds_swz(row)) & 3) * 16;
@@ -172,7 +176,7 @@ struct RingLoad {
     const int hw_out = a.Ho * a.Wo;
 #pragma unroll
     for (int j = 0; j < AJ; ++j) {
-      const int row = 16 * (4 * j + wave) + (lane >> 2);
+      const int row = 16 * (WAVES * j + wave) + (lane >> 2);
       const int grow = m0 + row;
       const bool ok = grow < a.M;
       const int rr = ok ? grow : a.M - 1;
@@ -185,14 +189,23 @@ struct RingLoad {
                 (((lane & 3) ^ lds_swz(row)) & 3) * 16;
     }
   }
+  // The walk at slab q of a tile.
+  __device__ inline void seek(const ConvArgs& a, int q) {
+    const int taps = a.R * a.S, chunk = q / taps, tap = q - chunk * taps;
+    ir = tap / a.S;
+    is = tap - ir * a.S;
+    ic = chunk * BK;
+    atap = ((int64_t)ir * a.W + is) * a.C + ic;
+    btap = tap * a.C + ic;
+  }
   // Issues load i (of kOps) of the next slab into stage (sa, sb).
   __device__ inline void load(const ConvArgs& a, int i, int8_t* sa, int8_t* sb, int wave) {
     if (i < AJ) {
       const bool ok = (unsigned)(aih[i] + ir) < (unsigned)a.H && (unsigned)(aiw[i] + is) < (unsigned)a.W;
       const int64_t p = ok ? arow[i] + atap : padp;
-      dma16(reinterpret_cast<const int8_t*>(p), &sa[(4 * i + wave) * 1024]);
+      dma16(reinterpret_cast<const int8_t*>(p), &sa[(WAVES * i + wave) * 1024]);
     } else {
-      dma16(bsrc[i - AJ] + btap, &sb[(4 * (i - AJ) + wave) * 1024]);
+      dma16(bsrc[i - AJ] + btap, &sb[(WAVES * (i - AJ) + wave) * 1024]);
     }
   }
   // Steps to the slab after; true when that was the tile's last slab (the walk
@@ -440,10 +453,93 @@ __device__ inline void slab_mfma(const int8_t* sa, const int8_t* sb, int row0, i
   slab_mfma<TM, TN>(sa, sb, row0, col0, lane, acc, [](int) {});
 }
 
+// A 32 T x 32 T tile (T = 1, 2) whose depth the block's four waves split: each
+// wave walks its quarter of the slabs through a ring of its own (three stages,
+// two slabs in flight; no barriers, a wave waits for its own loads only), then
+// the partial accumulators are added through LDS.  T = 2 leaves wave w with the
+// 32 x 32 subtile (w / 2, w % 2), T = 1 with its four accumulators per thread
+// 4 w .. 4 w + 3, in out[0 .. 3].
+constexpr int kSplitD = 2;  // slabs in flight
+template <int T>
+constexpr int kSplitStage = T * 64 * 64;  // bytes of a stage: 32 T rows, 32 T columns
+template <int T>
+constexpr int kSplitLds = 4 * (kSplitD + 1) * kSplitStage<T>;
+template <int T>
+__device__ __attribute__((always_inline)) inline void split_tile(const ConvArgs& a, int a_off, int m0,
+                                                                 int n0, int ktiles, int wave,
+                                                                 int lane, int8_t* lds, v16i& out) {
+  constexpr int D = kSplitD, ST = kSplitStage<T>, SA = 32 * T * 64;
+  const int q0 = (int)((int64_t)ktiles * wave / 4), n = (int)((int64_t)ktiles * (wave + 1) / 4) - q0;
+  int8_t* ring = lds + wave * (D + 1) * ST;
+  v16i acc[T][T];
+#pragma unroll
+  for (int t = 0; t < T * T; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[t / T][t % T][e] = 0;
+  using Ring = RingLoad<32 * T, 32 * T, 1>;
+  Ring ld;
+  constexpr int OPS = Ring::kOps, MFMAS = 2 * T * T, PER = (OPS + MFMAS - 1) / MFMAS;
+  ld.cols(a, a_off, n0, 0, lane);
+  ld.rows(a, m0, 0, lane);
+  ld.seek(a, q0);
+  for (int i = 0; i < D && i < n; ++i) (void)ld.issue(a, ring + i * ST, ring + i * ST + SA, 0);
+  int8_t* cur = ring;
+  for (int s = 0; s < n - D; ++s) {
+    wait_vmcnt<OPS*(D - 1)>();
+    asm volatile("" ::: "memory");
+    int8_t* st = cur == ring ? ring + D * ST : cur - ST;
+    slab_mfma<T, T>(cur, cur + SA, 0, 0, lane, acc, [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        if (i * PER + j < OPS) ld.load(a, i * PER + j, st, st + SA, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    (void)ld.advance(a);
+    cur = cur == ring + D * ST ? ring : cur + ST;
+  }
+  for (int left = min(D, n); left > 0; --left) {
+    if (left > 1) wait_vmcnt<OPS>();
+    else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    slab_mfma<T, T>(cur, cur + SA, 0, 0, lane, acc);
+    cur = cur == ring + D * ST ? ring : cur + ST;
+  }
+  // 16-byte pieces (wave, subtile t, group g of four accumulators, lane); the
+  // rings have been read
+  static_assert(4 * T * T * 4 * 64 * 16 <= kSplitLds<T>, "partial sums fit the rings");
+  __syncthreads();
+  v4i* red = reinterpret_cast<v4i*>(lds);
+#pragma unroll
+  for (int t = 0; t < T * T; ++t) {
+    const v16i& v = acc[t / T][t % T];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const v4i p = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+      if ((T == 2 ? t : g) != wave) red[((wave * T * T + t) * 4 + g) * 64 + lane] = p;
+      else
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[(T == 2 ? 4 * g : 0) + j] = p[j];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int o = 1; o < 4; ++o) {
+    const int from = (wave + o) & 3;
+#pragma unroll
+    for (int g = 0; g < (T == 2 ? 4 : 1); ++g) {
+      const v4i v = red[((from * T * T + (T == 2 ? wave : 0)) * 4 + (T == 2 ? g : wave)) * 64 + lane];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) out[4 * g + j] += v[j];
+    }
+  }
+}
+
 // Tile shape and grid of a conv; loader choice and the geometry in `a`.
 dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t* w,
                 const int32_t* colsum, const SrcDev* ep, ConvArgs& a, int& loader, int& cfg, int cus,
                 int halo = FXPQ_TILING_GEMM, bool wide_ok = true);
+// Grids that leave CUs idle: 64 x 64 or 32 x 32 tiles with split depth instead.
+void split_setup(ConvArgs& a, int& loader, int& cfg, dim3& grid, int cus);
 // The padded RGB layout with filter rows of at most 8 taps: re-lays the filters
 // into the handle's buffer and switches to the 16-byte pixel loader.
 void rgb8_setup(const Ctx& c, const fxpq_conv_desc& d, ConvArgs& a, int& loader);

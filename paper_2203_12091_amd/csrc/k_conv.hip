@@ -34,15 +34,17 @@ namespace fxpq {
 
 template <int BM, int BN, int TM, int TN, int MINW, int LOADER, int EPI>
 __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
-  constexpr int WGN = BN / (32 * TN);  // waves along N
-  static_assert((BM / (32 * TM)) * WGN == 4, "four waves per block");
-  constexpr int WROWS = 32 * TM, WCOLS = 32 * TN;
+  constexpr int SPLIT = split_t(LOADER);
+  constexpr int E = SPLIT == 1 ? 4 : 16;  // accumulators per thread and MFMA tile
+  constexpr int WROWS = 2 * E * TM, WCOLS = 32 * TN;
+  constexpr int WGN = BN / WCOLS;  // waves along N
+  static_assert((BM / WROWS) * WGN == 4, "four waves per block");
   constexpr int PER_THREAD = TM * TN * 16;
   // LDS slabs: two stages for the register-staged loaders; the ring of the
   // DMA loader is declared with it.
-  constexpr int NST = (LOADER == LD_DMA64) ? 1 : 2;
-  __shared__ __attribute__((aligned(16))) int8_t As[NST][BM * 64];
-  __shared__ __attribute__((aligned(16))) int8_t Bs[NST][BN * 64];
+  constexpr int NST = (LOADER == LD_DMA64 || SPLIT) ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) int8_t As[NST][SPLIT ? 16 : BM * 64];
+  __shared__ __attribute__((aligned(16))) int8_t Bs[NST][SPLIT ? 16 : BN * 64];
   __shared__ int rs_tab[128];
   __shared__ double shd[8];
   __shared__ WinShared wsh;
@@ -140,7 +142,11 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
   const int hw_out = a.Ho * a.Wo;
   const int taps = a.R * a.S;
 
-  if constexpr (LOADER == LD_DMA64) {
+  if constexpr (SPLIT != 0) {
+    __shared__ __attribute__((aligned(16))) int8_t ring[kSplitLds<SPLIT>];
+    epi_loads();
+    split_tile<SPLIT>(a, a_off, m0, n0, ktiles, wave, lane, ring, acc[0][0]);
+  } else if constexpr (LOADER == LD_DMA64) {
     RingLoad<BM, BN> ld;
     ld.cols(a, a_off, n0, wave, lane);
     ld.rows(a, m0, wave, lane);
@@ -327,7 +333,7 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 #pragma unroll
       for (int mi = 0; mi < TM; ++mi) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
+        for (int e = 0; e < E; ++e) {
           const int row = m0 + wm * WROWS + mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
           if (full || (row < a.M && col < a.K)) f(acc[mi][ni][e] + corr, Mc, Ac, row, col);
         }
@@ -361,7 +367,7 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi) {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
+          for (int e = 0; e < E; ++e) {
             const int lr = mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
             const bool ok = lr < vrows;
             const int v = acc[mi][ni][e];
@@ -389,7 +395,7 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi) {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
+          for (int e = 0; e < E; ++e) {
             const int v = acc[mi][ni][e];
             if constexpr (EPI == EPI_ACC)
               __builtin_amdgcn_raw_buffer_store_b32(
@@ -407,7 +413,7 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi) {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
+          for (int e = 0; e < E; ++e) {
             const int row = m0 + wm * WROWS + mi * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
             if (row < a.M && col < a.K) {
               const int v = acc[mi][ni][e];
@@ -475,8 +481,8 @@ static void conv_dispatch_loader(int loader, dim3 grid, hipStream_t st, const Co
     k_qconv<BM, BN, TM, TN, MINW, LD_DMA64, EPI><<<grid, 256, 0, st>>>(a);
   else if (loader == LD_GEN16)
     k_qconv<BM, BN, TM, TN, MINW, LD_GEN16, EPI><<<grid, 256, 0, st>>>(a);
-  else if (loader == LD_HALO4 || loader == LD_HALO8)
-    return;  // halo tiles have their own configurations
+  else if (loader == LD_HALO4 || loader == LD_HALO8 || split_t(loader) != 0)
+    return;  // these tiles have their own configurations
   else if constexpr (EPI == EPI_ACC && BN == 64) {
     if (loader == LD_RGB8) k_qconv<BM, BN, TM, TN, MINW, LD_RGB8, EPI><<<grid, 256, 0, st>>>(a);
     else k_qconv<BM, BN, TM, TN, MINW, LD_RGB4, EPI><<<grid, 256, 0, st>>>(a);
@@ -588,9 +594,40 @@ dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t
   }
 }
 
+// Split tiles where they all fit the chip at once: 32 x 32 tiles up to two per
+// CU (their LDS allows three), else 64 x 64 tiles up to one per CU (one fits).
+// Plain contraction with its min / max and predicted call, us, 128 x 128 or
+// 256 x 64 tiles / 64 x 64 / 32 x 32:
+//   64 x 4096 x 9216   51.7 60.5 / 28.7 33.2 / 20.5 24.4  (256 tiles of 32)
+//   8 x 512 x 4608     27.2 35.7 / 13.9 18.9 / 10.6 14.5  (16)
+//   392 x 512 x 4608   27.3 35.7 / 14.1 19.1 / 11.1 15.1  (208)
+//   1568 x 256 x 2304  18.3 26.0 / 11.6 16.4 / 11.3 15.7  (392)
+//   6272 x 128 x 1152  13.2 20.1 / 10.7 15.3 / 14.0 19.2  (784)
+//   25088 x 64 x 256   11.5 17.2 / 13.8 16.2 / --         (392 of 64)
+//   10816 x 384 x 1728 18.7 26.4 / 32.3 36.6 / --         (1014 of 64)
+void split_setup(ConvArgs& a, int& loader, int& cfg, dim3& grid, int cus) {
+  if (loader != LD_FAST64 && loader != LD_DMA64) return;
+  auto tiles = [&](int t) { return (int64_t)((a.M + t - 1) / t) * ((a.K + t - 1) / t); };
+  int t;
+  if (tiles(32) <= 2 * cus) t = 32;
+  else if (tiles(64) <= cus) t = 64;
+  else return;
+  loader = t == 32 ? LD_SPLIT32 : LD_SPLIT64;
+  cfg = t == 32 ? TC_32x32 : TC_64x64;
+  grid = dim3((a.M + t - 1) / t, (a.K + t - 1) / t);
+}
+
 template <int EPI>
 static void conv_run(const ConvArgs& a, int loader, int cfg, dim3 grid, hipStream_t st) {
   if constexpr (EPI == EPI_ACC) {
+    if (cfg == TC_64x64) {
+      k_qconv<64, 64, 1, 1, 1, LD_SPLIT64, EPI><<<grid, 256, 0, st>>>(a);
+      return;
+    }
+    if (cfg == TC_32x32) {
+      k_qconv<32, 32, 1, 1, 1, LD_SPLIT32, EPI><<<grid, 256, 0, st>>>(a);
+      return;
+    }
     if (cfg == TC_H224x256) {
       if (loader == LD_HALO4) k_qconv<224, 256, 7, 2, 1, LD_HALO4, EPI><<<grid, 256, 0, st>>>(a);
       else k_qconv<224, 256, 7, 2, 1, LD_HALO8, EPI><<<grid, 256, 0, st>>>(a);
@@ -617,7 +654,8 @@ hipError_t launch_conv(const Ctx& c, const fxpq_conv_desc& d, const void* x, int
   ConvArgs a{};
   int loader;
   int cfg;
-  const dim3 grid = conv_setup(d, x, x_type, w, colsum, ep, a, loader, cfg, c.cus, c.conv_tiling);
+  dim3 grid = conv_setup(d, x, x_type, w, colsum, ep, a, loader, cfg, c.cus, c.conv_tiling);
+  split_setup(a, loader, cfg, grid, c.cus);
   a.acc = acc;
   a.sink = c.sc.sink;
   a.want_mm = (ep != nullptr && d_minmax != nullptr);

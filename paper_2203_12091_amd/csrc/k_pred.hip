@@ -30,14 +30,18 @@ __device__ inline double uniform(double v) {
 
 template <int BM, int BN, int LOADER>
 __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
-  constexpr int TM = 2, TN = 2;        // 64 x 64 per wave
-  constexpr int WGN = BN / (32 * TN);  // waves along N
-  static_assert((BM / (32 * TM)) * WGN == 4, "four waves per block");
-  constexpr int WROWS = 32 * TM, WCOLS = 32 * TN;
-  constexpr int PER_THREAD = TM * TN * 16;  // values per thread and tile
+  constexpr int SPLIT = split_t(LOADER);
+  constexpr int TM = SPLIT ? 1 : 2, TN = TM;  // MFMA tiles per wave
+  constexpr int NG = SPLIT == 1 ? 1 : 4;      // groups of four accumulators per thread and tile
+  constexpr int WROWS = 8 * NG * TM, WCOLS = 32 * TN;
+  constexpr int WGN = BN / WCOLS;  // waves along N
+  static_assert((BM / WROWS) * WGN == 4, "four waves per block");
+  // bound on the values per thread and tile (one for all tile shapes, so that
+  // the decision does not depend on the shape)
+  constexpr int PER_THREAD = 64;
   constexpr int NST = (LOADER == LD_DMA64) ? 3 : 2;  // LDS stages
   constexpr int SA = BM * 64, SB = BN * 64;
-  __shared__ __attribute__((aligned(16))) int8_t stage[NST * (SA + SB)];
+  __shared__ __attribute__((aligned(16))) int8_t stage[SPLIT ? kSplitLds<SPLIT> : NST * (SA + SB)];
   __shared__ int rs_tab[128];
   __shared__ WinShared wsh;
 
@@ -184,7 +188,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
 #pragma unroll
       for (int mi = 0; mi < TM; ++mi) {
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+        for (int g = 0; g < NG; ++g) {
           int c[4];
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj) {
@@ -250,9 +254,9 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
       const int scol = n0 + wn * WCOLS + ni * 32 + ((lane & 31) & ~3);
       int rbase = m0 + wm * WROWS + 4 * (lane >> 5);
 #pragma nounroll
-      for (int it = 0; it < TM * 2; ++it, rbase += 16) {
+      for (int it = 0; it < (TM * NG + 1) / 2; ++it, rbase += 16) {
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
+        for (int g = 0; g < (NG < 2 ? NG : 2); ++g) {
           int c[4];
 #pragma unroll
           for (int jj = 0; jj < 4; ++jj) {
@@ -286,6 +290,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
+            if (NG == 1) break;
             if (e < 8) acc[mi][ni][e] = acc[mi][ni][e + 8];
             else if (mi + 1 < TM) acc[mi][ni][e] = acc[mi + 1][ni][e - 8];
           }
@@ -321,7 +326,15 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     return false;
   };
 
-  if constexpr (LOADER == LD_DMA64) {
+  if constexpr (SPLIT != 0) {
+    for (int tm = tm0; tm < tm1; ++tm) {
+      split_tile<SPLIT>(a, a_off, tm * BM, n0, ktiles, wave, lane, stage, acc[0][0]);
+#pragma unroll
+      for (int e = 0; e < 4 * NG; ++e) acc[0][0][e] += 128 * csum[0];
+      (void)finish_tile(tm);
+      __syncthreads();  // the sums have been read: the next tile's slabs may land
+    }
+  } else if constexpr (LOADER == LD_DMA64) {
     // Slab s of the block's sequence sits in stage s % NST; at step s the loads
     // of slab s have landed, those of s + 1 .. s + D - 1 and, issued at the
     // step, s + D are in flight, across tile ends too.  vmcnt counts in order
@@ -480,7 +493,8 @@ hipError_t launch_conv_pred(const Ctx& c, const fxpq_conv_desc& d, const void* x
   int cfg;
   // no 256 x 128 tiles: their 128 accumulators per thread and the window
   // state of this epilogue do not fit the registers of two blocks per CU
-  (void)conv_setup(d, x, x_type, w, colsum, &ep, a, loader, cfg, c.cus, FXPQ_TILING_GEMM, false);
+  dim3 grid = conv_setup(d, x, x_type, w, colsum, &ep, a, loader, cfg, c.cus, FXPQ_TILING_GEMM, false);
+  split_setup(a, loader, cfg, grid, c.cus);
   a.want_mm = 1;
   a.wl = wl;
   a.sign_req = sign;
@@ -506,7 +520,11 @@ hipError_t launch_conv_pred(const Ctx& c, const fxpq_conv_desc& d, const void* x
   a.flags = c.sc.flags;
   bool timed = timer_begin(c, FXPQ_TIMER_CBLOCK_PRED);
   rgb8_setup(c, d, a, loader);
-  if (cfg == TC_256x64) {
+  if (cfg == TC_64x64) {
+    pred_run<64, 64, LD_SPLIT64>(c, a);
+  } else if (cfg == TC_32x32) {
+    pred_run<32, 32, LD_SPLIT32>(c, a);
+  } else if (cfg == TC_256x64) {
     switch (loader) {
       case LD_FAST64: pred_run<256, 64, LD_FAST64>(c, a); break;
       case LD_GEN16: pred_run<256, 64, LD_GEN16>(c, a); break;
