@@ -465,74 +465,89 @@ constexpr int kSplitStage = T * 64 * 64;  // bytes of a stage: 32 T rows, 32 T c
 template <int T>
 constexpr int kSplitLds = 4 * (kSplitD + 1) * kSplitStage<T>;
 template <int T>
-__device__ __attribute__((always_inline)) inline void split_tile(const ConvArgs& a, int a_off, int m0,
-                                                                 int n0, int ktiles, int wave,
-                                                                 int lane, int8_t* lds, v16i& out) {
-  constexpr int D = kSplitD, ST = kSplitStage<T>, SA = 32 * T * 64;
-  const int q0 = (int)((int64_t)ktiles * wave / 4), n = (int)((int64_t)ktiles * (wave + 1) / 4) - q0;
-  int8_t* ring = lds + wave * (D + 1) * ST;
-  v16i acc[T][T];
-#pragma unroll
-  for (int t = 0; t < T * T; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[t / T][t % T][e] = 0;
+struct SplitTile {
+  static constexpr int D = kSplitD, ST = kSplitStage<T>, SA = 32 * T * 64;
   using Ring = RingLoad<32 * T, 32 * T, 1>;
+  static constexpr int OPS = Ring::kOps, MFMAS = 2 * T * T, PER = (OPS + MFMAS - 1) / MFMAS;
   Ring ld;
-  constexpr int OPS = Ring::kOps, MFMAS = 2 * T * T, PER = (OPS + MFMAS - 1) / MFMAS;
-  ld.cols(a, a_off, n0, 0, lane);
-  ld.rows(a, m0, 0, lane);
-  ld.seek(a, q0);
-  for (int i = 0; i < D && i < n; ++i) (void)ld.issue(a, ring + i * ST, ring + i * ST + SA, 0);
-  int8_t* cur = ring;
-  for (int s = 0; s < n - D; ++s) {
-    wait_vmcnt<OPS*(D - 1)>();
-    asm volatile("" ::: "memory");
-    int8_t* st = cur == ring ? ring + D * ST : cur - ST;
-    slab_mfma<T, T>(cur, cur + SA, 0, 0, lane, acc, [&](int i) __attribute__((always_inline)) {
-#pragma unroll
-      for (int j = 0; j < PER; ++j)
-        if (i * PER + j < OPS) ld.load(a, i * PER + j, st, st + SA, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    (void)ld.advance(a);
-    cur = cur == ring + D * ST ? ring : cur + ST;
+  int n;         // this wave's slabs
+  int8_t* ring;  // its stages
+
+  // Sends the first slabs' loads.
+  __device__ __attribute__((always_inline)) inline void start(const ConvArgs& a, int a_off, int m0,
+                                                              int n0, int ktiles, int wave,
+                                                              int lane, int8_t* lds) {
+    const int q0 = (int)((int64_t)ktiles * wave / 4);
+    n = (int)((int64_t)ktiles * (wave + 1) / 4) - q0;
+    ring = lds + wave * (D + 1) * ST;
+    ld.cols(a, a_off, n0, 0, lane);
+    ld.rows(a, m0, 0, lane);
+    ld.seek(a, q0);
+    for (int i = 0; i < D && i < n; ++i) (void)ld.issue(a, ring + i * ST, ring + i * ST + SA, 0);
   }
-  for (int left = min(D, n); left > 0; --left) {
-    if (left > 1) wait_vmcnt<OPS>();
-    else wait_vmcnt<0>();
-    asm volatile("" ::: "memory");
-    slab_mfma<T, T>(cur, cur + SA, 0, 0, lane, acc);
-    cur = cur == ring + D * ST ? ring : cur + ST;
+  __device__ __attribute__((always_inline)) inline void finish(const ConvArgs& a, int wave, int lane,
+                                                               int8_t* lds, v16i& out) {
+    v16i acc[T][T];
+#pragma unroll
+    for (int t = 0; t < T * T; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[t / T][t % T][e] = 0;
+    int8_t* cur = ring;
+    for (int s = 0; s < n - D; ++s) {
+      wait_vmcnt<OPS*(D - 1)>();
+      asm volatile("" ::: "memory");
+      int8_t* st = cur == ring ? ring + D * ST : cur - ST;
+      slab_mfma<T, T>(cur, cur + SA, 0, 0, lane, acc, [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+          if (i * PER + j < OPS) ld.load(a, i * PER + j, st, st + SA, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      (void)ld.advance(a);
+      cur = cur == ring + D * ST ? ring : cur + ST;
+    }
+    for (int left = min(D, n); left > 0; --left) {
+      if (left > 1) wait_vmcnt<OPS>();
+      else wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+      slab_mfma<T, T>(cur, cur + SA, 0, 0, lane, acc);
+      cur = cur == ring + D * ST ? ring : cur + ST;
+    }
+    add_waves(acc, wave, lane, lds, out);
   }
-  // 16-byte pieces (wave, subtile t, group g of four accumulators, lane); the
-  // rings have been read
-  static_assert(4 * T * T * 4 * 64 * 16 <= kSplitLds<T>, "partial sums fit the rings");
-  __syncthreads();
-  v4i* red = reinterpret_cast<v4i*>(lds);
+  __device__ __attribute__((always_inline)) static inline void add_waves(const v16i (&acc)[T][T],
+                                                                         int wave, int lane,
+                                                                         int8_t* lds, v16i& out) {
+    // 16-byte pieces (wave, subtile t, group g of four accumulators, lane); the
+    // rings have been read
+    static_assert(4 * T * T * 4 * 64 * 16 <= kSplitLds<T>, "partial sums fit the rings");
+    __syncthreads();
+    v4i* red = reinterpret_cast<v4i*>(lds);
 #pragma unroll
-  for (int t = 0; t < T * T; ++t) {
-    const v16i& v = acc[t / T][t % T];
+    for (int t = 0; t < T * T; ++t) {
+      const v16i& v = acc[t / T][t % T];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const v4i p = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-      if ((T == 2 ? t : g) != wave) red[((wave * T * T + t) * 4 + g) * 64 + lane] = p;
-      else
+      for (int g = 0; g < 4; ++g) {
+        const v4i p = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+        if ((T == 2 ? t : g) != wave) red[((wave * T * T + t) * 4 + g) * 64 + lane] = p;
+        else
 #pragma unroll
-        for (int j = 0; j < 4; ++j) out[(T == 2 ? 4 * g : 0) + j] = p[j];
+          for (int j = 0; j < 4; ++j) out[(T == 2 ? 4 * g : 0) + j] = p[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int o = 1; o < 4; ++o) {
+      const int from = (wave + o) & 3;
+#pragma unroll
+      for (int g = 0; g < (T == 2 ? 4 : 1); ++g) {
+        const v4i v = red[((from * T * T + (T == 2 ? wave : 0)) * 4 + (T == 2 ? g : wave)) * 64 + lane];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) out[4 * g + j] += v[j];
+      }
     }
   }
-  __syncthreads();
-#pragma unroll
-  for (int o = 1; o < 4; ++o) {
-    const int from = (wave + o) & 3;
-#pragma unroll
-    for (int g = 0; g < (T == 2 ? 4 : 1); ++g) {
-      const v4i v = red[((from * T * T + (T == 2 ? wave : 0)) * 4 + (T == 2 ? g : wave)) * 64 + lane];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) out[4 * g + j] += v[j];
-    }
-  }
-}
+};
 
 // Tile shape and grid of a conv; loader choice and the geometry in `a`.
 dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t* w,

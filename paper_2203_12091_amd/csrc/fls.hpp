@@ -108,6 +108,15 @@ struct FlsU {
   int ok;        // 0: non-finite input
 };
 
+// Largest k with x 2^k <= lim (x, lim > 0), from the exponents: lim has the
+// larger mantissa or loses one power.  (Trying every fl from the top took up
+// to 0.5 us at the start of each kernel of the search.)
+__host__ __device__ inline int pow2_room(double x, double lim) {
+  int ex, el;
+  const double fx = frexp(x, &ex), fl = frexp(lim, &el);
+  return el - ex - (fx > fl ? 1 : 0);
+}
+
 template <int KIND>
 __device__ inline FlsU fls_uniform(const SrcDev& s, const double* mm, int wl, int sign_req,
                                    int fl_lo, int fl_hi) {
@@ -124,13 +133,10 @@ __device__ inline FlsU fls_uniform(const SrcDev& s, const double* mm, int wl, in
   // largest fl with every value inside [qmin - 1/2, qmax + 1/2] after scaling
   u.beta_nosat = fl_lo - 1;
   if (u.ok) {
-    for (int b = fl_hi; b >= fl_lo; --b) {
-      double tmax = ldexp(mx, b - u.sv), tmin = ldexp(mn, b - u.sv);
-      if (tmax <= u.qmax + 0.5 && tmin >= u.qmin - 0.5) {
-        u.beta_nosat = b;
-        break;
-      }
-    }
+    int b = fl_hi;
+    if (mx > 0.0) b = min(b, u.sv + pow2_room(mx, u.qmax + 0.5));
+    if (mn < 0.0) b = min(b, u.sv + pow2_room(-mn, 0.5 - u.qmin));
+    if (b >= fl_lo) u.beta_nosat = b;
   }
   return u;
 }
@@ -151,9 +157,10 @@ struct WinSetup {
 // general pass.  Split sources (fp32, and int64 values, whose scale leaves
 // most of them beyond that bound) use the form W = Wh * 2^26 + Wl, exact while
 // 2^26 * max|q| * per_thread < 2^53, which the launcher's bound on per_thread
-// guarantees (51.4 M int64 values of a 16-bit first layer: 13.3 ms in the
-// general pass, see k_fls_general); beyond the unsplit bound they still have to lie within
-// the general pass's range, whose error they raise otherwise.
+// guarantees; beyond the unsplit bound they still have to lie within the
+// general pass's range, whose error they raise otherwise (51.4 M int64 values
+// of a 16-bit first layer took 13.3 ms in the general pass, 0.07 in the
+// window).
 constexpr bool win_split(int kind, int dt) {
   return kind == FXPQ_SRC_F32 || (kind == FXPQ_SRC_INT && dt == FXPQ_I64);
 }

@@ -144,8 +144,10 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 
   if constexpr (SPLIT != 0) {
     __shared__ __attribute__((aligned(16))) int8_t ring[kSplitLds<SPLIT>];
+    SplitTile<SPLIT> st;
     epi_loads();
-    split_tile<SPLIT>(a, a_off, m0, n0, ktiles, wave, lane, ring, acc[0][0]);
+    st.start(a, a_off, m0, n0, ktiles, wave, lane, ring);
+    st.finish(a, wave, lane, ring, acc[0][0]);
   } else if constexpr (LOADER == LD_DMA64) {
     RingLoad<BM, BN> ld;
     ld.cols(a, a_off, n0, wave, lane);

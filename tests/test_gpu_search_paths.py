@@ -79,3 +79,32 @@ def test_cblock_values_above_the_window(fx, h, orc, channels):
         above += float(np.max(v)) * 2.0 ** (ofl - 1 - s) > qmax + 0.5  # best fl more than one above no saturation
     assert above  # the fixture reaches the exact pass
     assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("wl", [2, 5, 8, 16])
+@pytest.mark.parametrize("shift", [0, 3, 9])
+def test_search_at_the_saturation_bound(fx, h, orc, wl, shift):
+    """The largest fl without saturation comes from the exponents of the min /
+    max: extremes exactly at the bounds qmax + 1/2 and qmin - 1/2 of an fl, and
+    one unit inside and outside, on either side."""
+    import torch
+    g = synth.rng_for(wl * 16 + shift, "bound")
+    s = 14
+    sd = torch.tensor([s], dtype=torch.int32, device=DEV)
+    for sign in (0, 1):
+        top = (2 ** (wl - sign) * 2 - 1) << shift        # 2 (qmax + 1/2)
+        bot = ((2 ** wl + 1) if sign else 1) << shift    # 2 (1/2 - qmin)
+        for du in (-1, 0, 1):
+            for mx, mn in ((top + du, 0), (top + du, -(bot // 2)), (top // 2, -(bot + du)),
+                           (0, -(bot + du))):
+                if sign == 0 and mn < 0 or mx == 0 and mn == 0:
+                    continue
+                v = g.integers(mn // 2, mx // 2 + 1, 300).astype(np.int64)
+                v[7], v[200] = mx, mn
+                vd = dev(v.astype(np.int32))
+                note("bound", wl, shift, sign, mx, mn)
+                out = fmt_new()
+                fx.fl_search(h, fx.src_int(vd, fx.I32, sd), v.size, wl, fx.SIGN_AUTO, FL_LO, FL_HI, out)
+                ofl, osign, _ = orc.fl_search_i64(v, s, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+                assert fmt_host(out) == (wl, ofl, osign, 0), (mx, mn)
+    assert fx.sync_status(h) == 0
