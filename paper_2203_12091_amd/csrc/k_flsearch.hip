@@ -481,7 +481,11 @@ __device__ inline int bitlen_i128(__int128 v) {
 }
 
 __device__ inline double i128_to_double(__int128 v) {
-  return (double)(long long)(v >> 64) * 0x1p64 + (double)(unsigned long long)v;
+  // by magnitude: the halves of a small negative value, -2^64 and 2^64 - |v|,
+  // lose its low bits
+  const unsigned __int128 m = v < 0 ? -(unsigned __int128)v : (unsigned __int128)v;
+  const double d = (double)(unsigned long long)(m >> 64) * 0x1p64 + (double)(unsigned long long)m;
+  return v < 0 ? -d : d;
 }
 
 // Decision of the window pass, taken by one wave from the slot sums.
