@@ -336,12 +336,31 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   // codes fit the dot product (signed, or no negative values).
   const int var = win ? win_variant(u, ws, a.mm) : 0;  // 2 NN + C0
   const bool fast = win && (var == 2 || (var == 0 && u.sign));
+  // Wave priorities: the two blocks of a CU run the same phases, and where both
+  // wait for one unit at once the other idles.  With the contraction ahead
+  // (deep: the matrix cores are what a tile waits for) or the epilogue ahead
+  // (shallow: vector arithmetic is) the blocks shift against each other.
+  // Batch 256, no priorities / contraction ahead / epilogue ahead: 28x28 128
+  // 3x3 67.8 / 62.5 / 65.2 us, 14x14 256 3x3 56.7 / 54.3 / 56.1, 28x28 512 -> 128
+  // 1x1 (8 slabs) 49.6 / 48.3 / 48.2, 14x14 256 -> 1024 1x1 (4 slabs) 62.9 / 63.1
+  // / 60.4, 28x28 128 -> 512 1x1 (2) 100.1 / 97.3 / 92.7, 56x56 64 -> 256 1x1
+  // (1) 170 / 169 / 162.
+  const bool deep = ktiles >= 8;
+  auto contraction_prio = [&]() __attribute__((always_inline)) {
+    if (deep) __builtin_amdgcn_s_setprio(2);
+    else __builtin_amdgcn_s_setprio(0);
+  };
+  auto epilogue_prio = [&]() __attribute__((always_inline)) {
+    if (deep) __builtin_amdgcn_s_setprio(0);
+    else __builtin_amdgcn_s_setprio(2);
+  };
   // Epilogue of row tile tm; true when it issued exactly TM * TN * 4 stores.
   // All of it is inlined: as a function of its own (the compiler's choice for
   // code of this size) it keeps this kernel's state in memory, and its
   // branches span more than a branch instruction reaches: their long form
   // takes the registers of the return address.
   auto finish_tile = [&](int tm) __attribute__((always_inline)) -> bool {
+    epilogue_prio();
     const int m0 = tm * BM;
     using F = std::false_type;
     using T = std::true_type;
@@ -418,6 +437,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
       ++s;
     };
     for (int tm = tm0; tm < tm1; ++tm) {
+      contraction_prio();
       acc_start();
       int kt = 0;
       while (kt < ktiles) {
@@ -437,6 +457,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     }
   } else {
     ld.lstore(stage, stage + SA, tid, padw);
+    contraction_prio();
     acc_start();
     __syncthreads();
     int tm = tm0, kt = 0;  // tile and slab being computed
@@ -453,6 +474,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
       if (++kt == ktiles) {
         kt = 0;
         (void)finish_tile(tm++);
+        contraction_prio();
         if (tm < tm1) acc_start();
       }
     }
