@@ -39,6 +39,7 @@ struct Scratch {
                             // (two sets, see fls_begin; a set is 0 when a search starts on it)
   unsigned long long* gen_part;  // general search partials [kMaxCand][kGenChunks][3]
   unsigned* gen_done;       // blocks of the general pass finished (0 between searches)
+  unsigned* ticket;         // blocks of a small reduction finished (0 between launches), or null
   void* plan;               // FlsPlan
   int32_t* sink;            // target of discarded stores [64]
   // deferred decisions of predicted calls: one record and one slot set per

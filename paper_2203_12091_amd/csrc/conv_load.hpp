@@ -98,6 +98,8 @@ struct ConvArgs {
   SrcDev ep;    // kind == FXPQ_SRC_ACC when an epilogue is given
   int has_ep;
   double* mm_part;
+  unsigned* mm_ticket;  // small grids: the last block writes the total to mm_out
+  double* mm_out;
   // EPI_ACC: store only when the FL-search plan asks for the general pass
   int only_if_general;
   const FlsPlan* plan_in;

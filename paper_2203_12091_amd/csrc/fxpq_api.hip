@@ -209,6 +209,7 @@ fxpq_status fxpq_create(fxpq_handle* out, int device) {
   size_t o_flags = take(4);
   size_t o_mm = take(2 * sizeof(double));
   size_t o_gd = take(4);
+  size_t o_ticket = take(4);
   size_t o_wp = take((size_t)2 * kWinSlots * kWinPart * sizeof(long long));
   size_t o_wpf = take((size_t)2 * kWinSlots * kWinPartF * sizeof(double));
   size_t o_psi = take((size_t)kMaxPredJobs * kWinSlots * kWinPart * sizeof(long long));
@@ -232,6 +233,7 @@ fxpq_status fxpq_create(fxpq_handle* out, int device) {
   h->sc.win_part_f = reinterpret_cast<double*>(base + o_wpf);
   h->sc.gen_part = reinterpret_cast<unsigned long long*>(base + o_gp);
   h->sc.gen_done = reinterpret_cast<unsigned*>(base + o_gd);
+  h->sc.ticket = reinterpret_cast<unsigned*>(base + o_ticket);
   h->sc.plan = base + o_plan;
   h->sc.sink = reinterpret_cast<int32_t*>(base + o_sink);
   h->sc.pred_jobs = reinterpret_cast<PredJob*>(base + o_jobs);
@@ -337,14 +339,7 @@ fxpq_status fxpq_fl_search(fxpq_handle h, const fxpq_src* src, int64_t n, int32_
   if (st) return st;
   if (n / ((int64_t)kThreads * kWinMaxPerThread) + 1 > kMaxFlsBlocks - 4096) return FXPQ_ERR_UNSUPPORTED;
   DeviceGuard g(h->device);
-  Ctx c = ctx(h);
-  const double* mm = src->d_minmax;
-  if (!mm) {
-    hipError_t e = launch_minmax(c, s, n, h->sc.minmax);
-    if (e != hipSuccess) return FXPQ_ERR_HIP;
-    mm = h->sc.minmax;
-  }
-  return hip_status(launch_fl_search(c, s, n, wl, sign, fl_lo, fl_hi, mm, d_fmt_out, d_sse));
+  return hip_status(launch_fl_search(ctx(h), s, n, wl, sign, fl_lo, fl_hi, src->d_minmax, d_fmt_out, d_sse));
 }
 
 fxpq_status fxpq_fl_search_static(const fxpq_src* src, int64_t n, int32_t wl, int32_t sign,
@@ -384,6 +379,7 @@ fxpq_status fxpq_fl_search_static(const fxpq_src* src, int64_t n, int32_t wl, in
   sc.flags = reinterpret_cast<unsigned*>(base + kSoFlags);
   sc.minmax = reinterpret_cast<double*>(base + kSoMinmax);
   sc.gen_done = reinterpret_cast<unsigned*>(base + kSoGenDone);
+  sc.ticket = nullptr;  // reductions finish in launches of their own
   sc.win_part = reinterpret_cast<long long*>(base + kSoWin);
   sc.win_part_f = reinterpret_cast<double*>(base + kSoWinF);
   sc.minmax_part = reinterpret_cast<double*>(base + kSoMmPart);
@@ -398,13 +394,7 @@ fxpq_status fxpq_fl_search_static(const fxpq_src* src, int64_t n, int32_t wl, in
   k_static_clear<<<1, 256, 0, c.stream>>>(reinterpret_cast<unsigned*>(base),
                                           (int)(kSoClearEnd / sizeof(unsigned)));
   if (hipGetLastError() != hipSuccess) return FXPQ_ERR_HIP;
-  const double* mm = src->d_minmax;
-  if (!mm) {
-    hipError_t e = launch_minmax(c, s, n, sc.minmax);
-    if (e != hipSuccess) return FXPQ_ERR_HIP;
-    mm = sc.minmax;
-  }
-  return hip_status(launch_fl_search(c, s, n, wl, sign, fl_lo, fl_hi, mm, d_fmt_out, d_sse));
+  return hip_status(launch_fl_search(c, s, n, wl, sign, fl_lo, fl_hi, src->d_minmax, d_fmt_out, d_sse));
 }
 
 fxpq_status fxpq_preprocess(fxpq_handle h, const fxpq_src* src, int64_t n, int32_t wl,

@@ -443,7 +443,9 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
     }
     mn = block_reduce(mn, OpMin(), shd);
     mx = block_reduce(mx, OpMax(), shd);
-    if (tid == 0) {
+    if (a.mm_ticket) {
+      ticket_minmax(mn, mx, bid, gridDim.x * gridDim.y, a.mm_part, a.mm_ticket, a.mm_out);
+    } else if (tid == 0) {
       a.mm_part[2 * bid] = mn;
       a.mm_part[2 * bid + 1] = mx;
     }
@@ -662,11 +664,14 @@ hipError_t launch_conv(const Ctx& c, const fxpq_conv_desc& d, const void* x, int
   a.sink = c.sc.sink;
   a.want_mm = (ep != nullptr && d_minmax != nullptr);
   a.mm_part = c.sc.minmax_part;
+  const int nb = (int)(grid.x * grid.y);
+  a.mm_ticket = ticket_for(c, nb);
+  a.mm_out = d_minmax;
   bool timed = timer_begin(c, FXPQ_TIMER_QCONV);
   rgb8_setup(c, d, a, loader);
   conv_run<EPI_ACC>(a, loader, cfg, grid, c.stream);
   timer_end(c, timed, 2.0 * (double)a.M * (double)d.k * (double)(d.r * d.s * d.c));
-  if (a.want_mm) return launch_minmax_fin(c, a.mm_part, (int)(grid.x * grid.y), d_minmax);
+  if (a.want_mm && !a.mm_ticket) return launch_minmax_fin(c, a.mm_part, nb, d_minmax);
   return hipGetLastError();
 }
 

@@ -969,35 +969,12 @@ __device__ void general_sums_decide(int wl, int sigma, const GenPlan& g,
 // unless the window pass left candidates undecided (and only then is the
 // device-scope release / acquire paid).
 template <int KIND, int DT>
-__global__ __launch_bounds__(kThreads) void k_fls_general(
-    SrcDev s, int64_t n, int wl, int fl_lo, int fl_hi, int nchunks, const double* mm, WinIn wi,
-    FlsPlan* plan, unsigned long long* part, unsigned* done, fxpq_fmt* out, double* d_sse,
-    unsigned* flags) {
+__device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, int fl_lo, int fl_hi,
+                                            int nchunks, const double* mm, const GenPlan& gp,
+                                            unsigned long long* part, unsigned* done,
+                                            fxpq_fmt* out, double* d_sse, unsigned* flags) {
   __shared__ unsigned long long shp[kThreads * 3];
   __shared__ int last;
-  __shared__ GenPlan gp_sh;
-  if (wi.ci && blockIdx.x == 0) win_slots_clear(wi.ci, wi.cf);
-  bool from_plan = true;
-  if (wi.decide) {
-    const WinSetup ws = win_setup<KIND, win_split(KIND, DT)>(s, mm, wl, wi.sign_req, fl_lo, fl_hi,
-                                                             wi.mode, wi.per_thread);
-    if (ws.verdict == 0) {  // else the window pass wrote the plan
-      from_plan = false;
-      if (threadIdx.x < 64) {
-        const WinResult r = win_decide(ws, wi.nce, fl_hi, wi.pi, wi.pf);
-        if (threadIdx.x == 0) {
-          if (blockIdx.x == 0) win_record(ws, r, wl, wi.codes, plan, out);
-          gp_sh = GenPlan{r.done ? 0 : 1, 0, ws.u.sign, ws.b1 + 1, r.gen_hi, r.fl_win};
-        }
-      }
-    }
-  }
-  if (from_plan && threadIdx.x == 0)
-    gp_sh = GenPlan{plan->need_general, plan->status, plan->sign, plan->gen_lo, plan->gen_hi,
-                    plan->gen_extra};
-  __syncthreads();
-  const GenPlan gp = gp_sh;
-  if (!gp.need || gp.status) return;
   const int sign = gp.sign;
   const int glo = gp.glo, ghi = gp.ghi, extra = gp.extra;
   const int nreg = ghi - glo + 1;
@@ -1126,6 +1103,119 @@ __global__ __launch_bounds__(kThreads) void k_fls_general(
   __threadfence();
   general_decide(wl, fl_lo, fl_hi, nchunks, sigma, gp, part, out, d_sse);
   if (threadIdx.x == 0) *done = 0u;  // ready for the next search
+}
+
+template <int KIND, int DT>
+__global__ __launch_bounds__(kThreads) void k_fls_general(
+    SrcDev s, int64_t n, int wl, int fl_lo, int fl_hi, int nchunks, const double* mm, WinIn wi,
+    FlsPlan* plan, unsigned long long* part, unsigned* done, fxpq_fmt* out, double* d_sse,
+    unsigned* flags) {
+  __shared__ GenPlan gp_sh;
+  if (wi.ci && blockIdx.x == 0) win_slots_clear(wi.ci, wi.cf);
+  bool from_plan = true;
+  if (wi.decide) {
+    const WinSetup ws = win_setup<KIND, win_split(KIND, DT)>(s, mm, wl, wi.sign_req, fl_lo, fl_hi,
+                                                             wi.mode, wi.per_thread);
+    if (ws.verdict == 0) {  // else the window pass wrote the plan
+      from_plan = false;
+      if (threadIdx.x < 64) {
+        const WinResult r = win_decide(ws, wi.nce, fl_hi, wi.pi, wi.pf);
+        if (threadIdx.x == 0) {
+          if (blockIdx.x == 0) win_record(ws, r, wl, wi.codes, plan, out);
+          gp_sh = GenPlan{r.done ? 0 : 1, 0, ws.u.sign, ws.b1 + 1, r.gen_hi, r.fl_win};
+        }
+      }
+    }
+  }
+  if (from_plan && threadIdx.x == 0)
+    gp_sh = GenPlan{plan->need_general, plan->status, plan->sign, plan->gen_lo, plan->gen_hi,
+                    plan->gen_extra};
+  __syncthreads();
+  const GenPlan gp = gp_sh;
+  if (!gp.need || gp.status) return;
+  general_run<KIND, DT>(s, n, wl, fl_lo, fl_hi, nchunks, mm, gp, part, done, out, d_sse, flags);
+}
+
+// Search of a small tensor in one launch of one block: the min / max (unless
+// given), the window's sums in LDS slots, the decision, and the exact pass when
+// it leaves candidates.  Bound by the latency of its steps; the four launches
+// it replaces (min / max and its finish, window, decision) are mostly launch.
+// int64 values leave the exact pass to its own launch: beyond 2^52 it works in
+// 128 bits, candidate by candidate, far too long for one block.
+constexpr bool small_general(int kind, int dt) { return !(kind == FXPQ_SRC_INT && dt == FXPQ_I64); }
+
+template <int KIND, int DT>
+__global__ __launch_bounds__(kThreads) void k_search_small(
+    SrcDev s, int64_t n, int wl, int sign_req, int fl_lo, int fl_hi, int64_t per_thread,
+    const double* mm_in, double* mm_out, FlsPlan* plan, unsigned long long* part,
+    unsigned* done, fxpq_fmt* out, unsigned* flags) {
+  using PK = Pack<KIND, DT>;
+  __shared__ double mm[2], sh[8];
+  __shared__ WinShared wsh;
+  __shared__ long long slot_i[kWinSlots * kWinPart];
+  __shared__ double slot_f[kWinSlots * kWinPartF];
+  __shared__ GenPlan gp_sh;
+  win_slots_clear(slot_i, slot_f);
+  if (mm_in) {
+    if (threadIdx.x < 2) mm[threadIdx.x] = mm_in[threadIdx.x];
+  } else {
+    double mn = INFINITY, mx = -INFINITY;
+    bool bad = false;
+    auto add = [&](double v) {
+      mn = fmin(mn, v);
+      mx = fmax(mx, v);
+      if (KIND == FXPQ_SRC_F32) bad |= !isfinite(v);
+    };
+    ThreadVals<PK::V> t;
+    thread_vals_init<KIND, DT>(s, 0, t);
+    stream_values<KIND, DT>(s, n, t, [&](double v, int64_t) { add(v); });
+    if (threadIdx.x == 0)
+      for (int64_t i = n - n % PK::EP; i < n; ++i) add(load1<KIND, DT>(s, i));
+    const int any_bad = __syncthreads_or(bad);
+    mn = block_reduce(mn, OpMin(), sh);
+    mx = block_reduce(mx, OpMax(), sh);
+    if (threadIdx.x == 0) {
+      mm_out[0] = mm[0] = any_bad ? NAN : mn;
+      mm_out[1] = mm[1] = mx;
+      if (any_bad) raise_flag(flags, FXPQ_FLAG_NONFINITE);
+    }
+  }
+  __syncthreads();
+  constexpr int NB = kCeBounds;
+  const WinSetup ws = win_setup<KIND, win_split(KIND, DT)>(s, mm, wl, sign_req, fl_lo, fl_hi,
+                                                           MODE_SEARCH, per_thread);
+  if (ws.verdict != 0) {
+    if (threadIdx.x == 0) {
+      win_verdict_write(ws, wl, fl_lo, fl_hi, plan, out, flags);
+      gp_sh = GenPlan{plan->need_general, plan->status, plan->sign, plan->gen_lo, plan->gen_hi,
+                      plan->gen_extra};
+    }
+  } else {
+    WinAcc acc;
+    const WinCodes wcd{};
+    switch (win_variant(ws.u, ws, mm)) {
+      case 0: win_loop<KIND, DT, false, false, NB, false>(s, n, ws.u, ws, wcd, acc); break;
+      case 1: win_loop<KIND, DT, false, true, NB, false>(s, n, ws.u, ws, wcd, acc); break;
+      case 2: win_loop<KIND, DT, true, false, NB, false>(s, n, ws.u, ws, wcd, acc); break;
+      default: win_loop<KIND, DT, true, true, NB, false>(s, n, ws.u, ws, wcd, acc); break;
+    }
+    if constexpr (win_split(KIND, DT)) win_write_partials(acc, NB, 0, slot_i, slot_f, wsh);
+    else win_write_partials_int(acc, NB, 0, slot_i, slot_f, wsh);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      const WinResult r = win_decide(ws, NB, fl_hi, slot_i, slot_f);
+      if (threadIdx.x == 0) {
+        win_record(ws, r, wl, 0, plan, out);
+        gp_sh = GenPlan{r.done ? 0 : 1, 0, ws.u.sign, ws.b1 + 1, r.gen_hi, r.fl_win};
+      }
+    }
+  }
+  if constexpr (small_general(KIND, DT)) {
+    __syncthreads();
+    const GenPlan gp = gp_sh;
+    if (!gp.need || gp.status) return;
+    general_run<KIND, DT>(s, n, wl, fl_lo, fl_hi, 1, mm, gp, part, done, out, nullptr, flags);
+  }
 }
 
 // One block: totals per candidate, exact comparison, ties to the larger fl.
@@ -1287,8 +1377,39 @@ static hipError_t fl_search_passes(const Ctx& c, const SrcDev& s, int64_t n, int
   return general_pass(c, s, n, wl, fl_lo, fl_hi, d_minmax, wi, out, d_sse);
 }
 
+// Tensors that one block searches in one launch (k_search_small): up to
+// kSmallSearch values (us with the min / max to find, one launch / four: n =
+// 256 9.2 / 15.1, 4096 10.6 / 16.3, 8192 12.8 / 16.8, 16384 17.2 / 16.7; half of
+// that when it is given: 256 7.6 / 8.8, 4096 8.6 / 9.4, 8192 10.1 / 9.6), word lengths of the window; C-Block values with the
+// thread's channels fixed over one block's stride; fp32 only for fl_hi that
+// keep ordinary values (below 4096) out of the 128-bit pass.
+constexpr int64_t kSmallSearch = 8192;
+static bool small_search(const SrcDev& s, int64_t n, int wl, int fl_hi, bool have_mm) {
+  return n <= (have_mm ? kSmallSearch / 2 : kSmallSearch) && wl >= 2 && wl <= 16 &&
+         (s.kind != FXPQ_SRC_ACC || kThreads * 4 % s.channels == 0) &&
+         (s.kind != FXPQ_SRC_F32 || fl_hi <= 16);
+}
+
 hipError_t launch_fl_search(const Ctx& c, const SrcDev& s, int64_t n, int wl, int sign, int fl_lo,
                             int fl_hi, const double* d_minmax, fxpq_fmt* out, double* d_sse) {
+  if (!d_sse && small_search(s, n, wl, fl_hi, d_minmax != nullptr)) {
+    const int vec = (s.kind == FXPQ_SRC_ADD) ? 16 : 4;
+    const double elem = (s.kind == FXPQ_SRC_ADD) ? 2.0 : (s.kind == FXPQ_SRC_INT && s.dtype == FXPQ_I64) ? 8.0 : 4.0;
+    FlsPlan* plan = static_cast<FlsPlan*>(c.sc.plan);
+    bool timed = timer_begin(c, FXPQ_TIMER_FLS_WINDOW);
+    FXPQ_DISPATCH_SRC(s.kind, s.dtype,
+                      (k_search_small<K_, D_><<<1, kThreads, 0, c.stream>>>(
+                          s, n, wl, sign, fl_lo, fl_hi, window_per_thread(n, 1, vec), d_minmax,
+                          c.sc.minmax, plan, c.sc.gen_part, c.sc.gen_done, out, c.sc.flags)));
+    timer_end(c, timed, elem * (double)n);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess || small_general(s.kind, s.dtype)) return e;
+    return launch_fls_general(c, s, n, wl, fl_lo, fl_hi, d_minmax ? d_minmax : c.sc.minmax, out, nullptr);
+  }
+  if (!d_minmax) {
+    hipError_t e = launch_minmax(c, s, n, c.sc.minmax);
+    if (e != hipSuccess) return e;
+    d_minmax = c.sc.minmax;
+  }
   return fl_search_passes(c, s, n, wl, sign, fl_lo, fl_hi, d_minmax, out, d_sse, nullptr, nullptr);
 }
 

@@ -68,6 +68,7 @@ int stream_grid(int64_t n, int channels, int64_t max_per_thread, int vec, int re
 // ----------------------------------------------------------------------------
 template <int KIND, int DT>
 __global__ __launch_bounds__(kThreads) void k_minmax(SrcDev s, int64_t n, double* part,
+                                                     unsigned* ticket, double* out,
                                                      unsigned* flags) {
   __shared__ double sh[8];
   using PK = Pack<KIND, DT>;
@@ -121,10 +122,13 @@ __global__ __launch_bounds__(kThreads) void k_minmax(SrcDev s, int64_t n, double
   int any_bad = __syncthreads_or(bad);
   mn = block_reduce(mn, OpMin(), sh);
   mx = block_reduce(mx, OpMax(), sh);
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = any_bad ? NAN : mn;
+  if (threadIdx.x == 0 && any_bad) raise_flag(flags, FXPQ_FLAG_NONFINITE);
+  if (any_bad) mn = NAN;
+  if (ticket) {
+    ticket_minmax(mn, mx, blockIdx.x, gridDim.x, part, ticket, out);
+  } else if (threadIdx.x == 0) {
+    part[2 * blockIdx.x] = mn;
     part[2 * blockIdx.x + 1] = mx;
-    if (any_bad) raise_flag(flags, FXPQ_FLAG_NONFINITE);
   }
 }
 
@@ -281,10 +285,22 @@ __device__ inline double code_at(const void* codes, int64_t i) {
   else return static_cast<const int8_t*>(codes)[i];
 }
 
+// Squared error, extremes and standard deviation from the sums.
+__device__ inline void layer_error_out(double sse, double mn, double mx, double s1, double s2,
+                                       int64_t n, double* out) {
+  const double mean = s1 / (double)n;
+  const double var = s2 / (double)n - mean * mean;
+  out[0] = sse;
+  out[1] = mn;
+  out[2] = mx;
+  out[3] = sqrt(var > 0.0 ? var : 0.0);
+}
+
 template <int CT>
 __global__ __launch_bounds__(kThreads) void k_layer_error(const float* ref, const void* codes,
                                                           const fxpq_fmt* fmt, int64_t n,
-                                                          double* part) {
+                                                          double* part, unsigned* ticket,
+                                                          double* out) {
   __shared__ double sh[8];
   // fp32 values (CT == FXPQ_F32) are compared as they are
   const double step = (CT == FXPQ_F32) ? 1.0 : ldexp(1.0, -fmt->fl);
@@ -318,7 +334,21 @@ __global__ __launch_bounds__(kThreads) void k_layer_error(const float* ref, cons
   mx = block_reduce(mx, OpMax(), sh);
   s1 = block_reduce(s1, OpAddD(), sh);
   s2 = block_reduce(s2, OpAddD(), sh);
-  if (threadIdx.x == 0) {
+  if (ticket) {
+    if (threadIdx.x == 0) {
+      const double q[5] = {sse, mn, mx, s1, s2};
+      for (int k = 0; k < 5; ++k) ticket_publish(part + 5 * blockIdx.x + k, q[k]);
+    }
+    if (!ticket_last(ticket, gridDim.x) || threadIdx.x >= 64) return;
+    const bool in = threadIdx.x < gridDim.x;
+    const double* p = part + 5 * threadIdx.x;
+    sse = wave_reduce(in ? ticket_read(p) : 0.0, OpAddD());
+    mn = wave_reduce(in ? ticket_read(p + 1) : INFINITY, OpMin());
+    mx = wave_reduce(in ? ticket_read(p + 2) : -INFINITY, OpMax());
+    s1 = wave_reduce(in ? ticket_read(p + 3) : 0.0, OpAddD());
+    s2 = wave_reduce(in ? ticket_read(p + 4) : 0.0, OpAddD());
+    if (threadIdx.x == 0) layer_error_out(sse, mn, mx, s1, s2, n, out);
+  } else if (threadIdx.x == 0) {
     double* p = part + 5 * blockIdx.x;
     p[0] = sse; p[1] = mn; p[2] = mx; p[3] = s1; p[4] = s2;
   }
@@ -341,14 +371,7 @@ __global__ __launch_bounds__(kThreads) void k_layer_error_fin(const double* part
   c = block_reduce(c, OpMax(), sh);
   d = block_reduce(d, OpAddD(), sh);
   e = block_reduce(e, OpAddD(), sh);
-  if (threadIdx.x == 0) {
-    double mean = d / (double)n;
-    double var = e / (double)n - mean * mean;
-    out[0] = a;
-    out[1] = b;
-    out[2] = c;
-    out[3] = sqrt(var > 0.0 ? var : 0.0);
-  }
+  if (threadIdx.x == 0) layer_error_out(a, b, c, d, e, n, out);
 }
 
 // ----------------------------------------------------------------------------
@@ -503,10 +526,10 @@ hipError_t launch_minmax(const Ctx& c, const SrcDev& s, int64_t n, double* out) 
   FXPQ_DISPATCH_SRC(s.kind, s.dtype,
                     (blocks = stream_grid(n, src_channels(s), 0, src_vec(s),
                                           resident_blocks(c, (const void*)&k_minmax<K_, D_>)),
-                     k_minmax<K_, D_><<<blocks, kThreads, 0, c.stream>>>(s, n, c.sc.minmax_part,
-                                                                        c.sc.flags)));
-  k_minmax_fin<<<1, kMmFinThreads, 0, c.stream>>>(c.sc.minmax_part, blocks, out);
-  return hipGetLastError();
+                     k_minmax<K_, D_><<<blocks, kThreads, 0, c.stream>>>(
+                         s, n, c.sc.minmax_part, ticket_for(c, blocks), out, c.sc.flags)));
+  if (ticket_for(c, blocks)) return hipGetLastError();
+  return launch_minmax_fin(c, c.sc.minmax_part, blocks, out);
 }
 
 // Requantization of C-Block values, plus the min / max of the residual sum
@@ -636,7 +659,7 @@ hipError_t launch_layer_error(const Ctx& c, const float* ref, const void* codes,
   double* part = c.sc.minmax_part;  // 5 doubles per block fits (kMaxConvBlocks * 2)
   auto run = [&](auto kernel) {
     const int blocks = stream_grid(n, 0, 0, 4, resident_blocks(c, (const void*)kernel));
-    kernel<<<blocks, kThreads, 0, c.stream>>>(ref, codes, fmt, n, part);
+    kernel<<<blocks, kThreads, 0, c.stream>>>(ref, codes, fmt, n, part, ticket_for(c, blocks), out);
     return blocks;
   };
   int blocks;
@@ -649,7 +672,7 @@ hipError_t launch_layer_error(const Ctx& c, const float* ref, const void* codes,
     case FXPQ_F32: blocks = run(&k_layer_error<FXPQ_F32>); break;
     default: blocks = run(&k_layer_error<FXPQ_I8>); break;
   }
-  k_layer_error_fin<<<1, kThreads, 0, c.stream>>>(part, blocks, n, out);
+  if (!ticket_for(c, blocks)) k_layer_error_fin<<<1, kThreads, 0, c.stream>>>(part, blocks, n, out);
   return hipGetLastError();
 }
 

@@ -454,6 +454,60 @@ struct OpMaxU {
   }
 };
 
+// ---- small grids: the last block finishes the reduction ---------------------
+// Block partials leave as device-scope exchanges (performed at the memory side
+// once their old value is back), then the block draws a ticket; the block that
+// draws the last one reads all partials with device-scope loads.  No fence: one
+// would write back the chip's second-level caches.  Up to kTicketBlocks blocks:
+// tickets serialize at about 12 ns each (256 blocks 5.6 us, as long as the
+// finish in a launch of its own; 64 blocks 3.5, 8 blocks 3.0).
+constexpr int kTicketBlocks = 64;
+static inline unsigned* ticket_for(const Ctx& c, int64_t blocks) {
+  return blocks <= kTicketBlocks ? c.sc.ticket : nullptr;
+}
 
+__device__ inline void ticket_publish(double* p, double v) {
+  const unsigned long long old =
+      __hip_atomic_exchange(reinterpret_cast<unsigned long long*>(p),
+                            (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" ::"v"(old) : "memory");  // waits for it
+}
+__device__ inline double ticket_read(const double* p) {
+  return __longlong_as_double((long long)__hip_atomic_load(
+      reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// Called by every thread after thread 0 published the block's partials: true
+// in the block that drew the last of `blocks` tickets (which are then back at
+// zero for the next launch).
+__device__ inline bool ticket_last(unsigned* ticket, unsigned blocks) {
+  __shared__ int last;
+  if (threadIdx.x == 0) {
+    last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == blocks - 1;
+    if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  return last;
+}
+// Block (min, max) partial of a ticket reduction; the last block writes the
+// total to out (a NaN minimum marks non-finite input).
+__device__ inline void ticket_minmax(double mn, double mx, int bid, int blocks, double* part,
+                                     unsigned* ticket, double* out) {
+  if (threadIdx.x == 0) {
+    ticket_publish(part + 2 * bid, mn);
+    ticket_publish(part + 2 * bid + 1, mx);
+  }
+  if (!ticket_last(ticket, blocks) || threadIdx.x >= 64) return;
+  const int i = threadIdx.x;
+  const double a = i < blocks ? ticket_read(part + 2 * i) : INFINITY;
+  const double b = i < blocks ? ticket_read(part + 2 * i + 1) : -INFINITY;
+  const bool bad = __any(isnan(a));
+  mn = wave_reduce(a, OpMin());
+  mx = wave_reduce(b, OpMax());
+  if (threadIdx.x == 0) {
+    out[0] = bad ? NAN : mn;
+    out[1] = mx;
+  }
+}
 
 }  // namespace fxpq
