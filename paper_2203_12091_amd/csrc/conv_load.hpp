@@ -125,6 +125,8 @@ struct ConvArgs {
   // Ho), hTPI tiles per image (hG == 1), input patch hPH x hPW per image;
   // stores of rows that do not exist go to `sink` (32 int32)
   int hG, hTH, hTPI, hPH, hPW;
+  // RGB8: 16-byte chunks (four taps) per filter row; four chunks as rows and chunks
+  int rgb_chunks, rgb_step_r, rgb_step_c;
   int32_t* sink;
 };
 
@@ -253,7 +255,11 @@ struct StagedLoad {
   const int8_t* bptr[BCH];
   v4i regA[ACH], regB[BCH];
   bool aok[ACH], bok[BCH];
-  int rgb_d[ACH];  // LD_RGB8: dword shift of the loaded pixels (0 inside)
+  // LD_RGB8: pixel index of the row at (ih0, 0) within its image, dword shift of
+  // the loaded pixels (0 inside the image), the next chunk's filter row and its
+  // chunk within the row
+  int rgb_p[ACH], rgb_d[ACH];
+  int rgb_r, rgb_c;
   int kt;          // next slab of the tile
   // LD_FAST64, LD_GEN16: filter tap and channel of the next chunk (uniform /
   // per thread), advanced slab by slab
@@ -282,6 +288,15 @@ struct StagedLoad {
     }
     kt = 0;
     ir = is = ic = 0;
+    if constexpr (LOADER == LD_RGB8) {
+      rgb_r = (tid & 3) / a.rgb_chunks;
+      rgb_c = (tid & 3) - rgb_r * a.rgb_chunks;
+#pragma unroll
+      for (int i = 0; i < ACH; ++i) {
+        rgb_p[i] = ih0[i] * a.W;
+        if (!aval[i]) ih0[i] = INT_MIN / 2;  // no row: never inside
+      }
+    }
     if constexpr (LOADER == LD_GEN16) {
       ic = (tid & 3) * 16;
       wrap(a);
@@ -331,26 +346,28 @@ struct StagedLoad {
       ic += BK;
       wrap(a);
     } else if constexpr (LOADER == LD_RGB8) {
-      // filters re-laid as [r][s < 8][c]: chunk q = 4 kt + kc is filter
-      // row q / 2, taps 4 (q % 2) .. + 3, i.e. four neighbouring pixels of
-      // one input row: one 16-byte load of the four pixels from column
-      // iw clamped to [0, W - 4] (W >= 4); at the image borders the LDS
-      // store shifts them by d = iw - that column and pads the pixels
-      // outside the row (the taps past S have zero weights: their pixels
-      // only need to be readable).  Rows past R are zero filter rows; a
-      // row outside the image is all padding (d = 8).
-      const int q = kt * 4 + kc;
-      const int r = q >> 1, s0 = (q & 1) * 4;
+      // filters re-laid as [r][chunk][4 taps][c] (rgb8_setup): a chunk is four
+      // neighbouring pixels of one input row, one 16-byte load from column iw
+      // clamped to [0, W - 4] (W >= 4); at the image borders the LDS store
+      // shifts them and pads the pixels outside the row (the taps past S have
+      // zero weights: their pixels only need to be readable).  Rows past R are
+      // zero filter rows; a row outside the image is all padding (shift 8).
+      const int r = rgb_r < a.R ? rgb_r : INT_MIN / 2, rw = rgb_r * a.W;
 #pragma unroll
       for (int i = 0; i < ACH; ++i) {
-        const int ih = ih0[i] + r, iw = iw0[i] + s0;
-        const bool rowok = aval[i] && r < a.R && ih >= 0 && ih < a.H;
-        const int iwc = min(max(iw, 0), a.W - 4);
-        const int64_t off = rowok ? ((int64_t)ih * a.W + iwc) * 4 : 0;
-        regA[i] = *reinterpret_cast<const v4i_a4*>(abase[i] + off);
-        rgb_d[i] = rowok ? iw - iwc : 8;
+        const int iw = iw0[i] + 4 * rgb_c, iwc = min(max(iw, 0), a.W - 4);
+        const bool ok = (unsigned)(ih0[i] + r) < (unsigned)a.H;
+        const unsigned px = ok ? (unsigned)(rgb_p[i] + rw + iwc) : 0u;
+        regA[i] = *reinterpret_cast<const v4i_a4*>(abase[i] + (uint64_t)px * 4);
+        rgb_d[i] = ok ? iw - iwc : 8;
         aok[i] = true;
       }
+      // four chunks on
+      rgb_r += a.rgb_step_r;
+      rgb_c += a.rgb_step_c;
+      const bool wrap_c = rgb_c >= a.rgb_chunks;
+      rgb_c -= wrap_c ? a.rgb_chunks : 0;
+      rgb_r += wrap_c;
     } else {  // LD_RGB4: four 4-byte pixels per 16-byte chunk
 #pragma unroll
       for (int i = 0; i < ACH; ++i) {
@@ -557,8 +574,9 @@ dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t
                 int halo = FXPQ_TILING_GEMM, bool wide_ok = true);
 // Grids that leave CUs idle: 64 x 64 or 32 x 32 tiles with split depth instead.
 void split_setup(ConvArgs& a, int& loader, int& cfg, dim3& grid, int cus);
-// The padded RGB layout with filter rows of at most 8 taps: re-lays the filters
-// into the handle's buffer and switches to the 16-byte pixel loader.
+// The padded RGB layout: re-lays the filters into the handle's buffer, filter
+// rows padded to whole 16-byte chunks of four taps, and switches to the loader
+// that reads four pixels at a time.
 void rgb8_setup(const Ctx& c, const fxpq_conv_desc& d, ConvArgs& a, int& loader);
 
 }  // namespace fxpq

@@ -23,7 +23,12 @@ CASES = [
     (5, 16, 165, 163, 64, 3, 1, 1, False, False),   # C % 16
     (21, 32, 57, 57, 100, 1, 1, 0, True, False),    # C % 16, 128 columns, ragged
     (11, 3, 223, 221, 64, 7, 2, 3, False, False),   # padded RGB, 16-byte pixels
-    (11, 3, 223, 221, 32, 11, 2, 5, True, True),    # padded RGB, filter rows past 8 taps
+    (11, 3, 223, 221, 32, 11, 2, 5, True, True),    # padded RGB, three chunks per filter row
+    (3, 3, 50, 47, 64, 3, 1, 1, False, True),       # one chunk
+    (2, 3, 33, 61, 36, 9, 1, 4, False, False),      # three chunks, ragged columns
+    (1, 3, 64, 64, 24, 5, 1, 2, True, False),       # two
+    (2, 3, 40, 37, 128, 11, 1, 5, True, True),      # filters too large to re-lay: pixel by pixel
+    (5, 3, 37, 3, 64, 3, 1, 1, False, False),       # rows narrower than a chunk
 ]
 
 
