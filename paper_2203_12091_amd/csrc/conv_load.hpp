@@ -39,10 +39,19 @@ __device__ inline int lds_off(int row, int chunk) {
 // (up to 256 / 512 pixels per channel chunk) is loaded into LDS once and read
 // by every filter tap, weights through the DMA ring.  SPLIT64, SPLIT32:
 // C % 64 == 0, 64 x 64 / 32 x 32 tiles whose depth the four waves split
-// (split_tile).
+// (SplitTile).  DMA16, SPLIT64G, SPLIT32G: the same for C % 16 == 0.
 enum Loader { LD_FAST64 = 0, LD_GEN16 = 1, LD_RGB4 = 2, LD_DMA64 = 3, LD_HALO4 = 4, LD_HALO8 = 5,
-              LD_RGB8 = 6, LD_SPLIT64 = 7, LD_SPLIT32 = 8 };
-constexpr int split_t(int loader) { return loader == LD_SPLIT64 ? 2 : (loader == LD_SPLIT32 ? 1 : 0); }
+              LD_RGB8 = 6, LD_SPLIT64 = 7, LD_SPLIT32 = 8, LD_DMA16 = 9, LD_SPLIT64G = 10,
+              LD_SPLIT32G = 11 };
+constexpr int split_t(int loader) {
+  return loader == LD_SPLIT64 || loader == LD_SPLIT64G ? 2
+         : (loader == LD_SPLIT32 || loader == LD_SPLIT32G ? 1 : 0);
+}
+// Loaders through the LDS ring of whole blocks; any C % 16 == 0 (not only 64).
+constexpr bool is_ring(int loader) { return loader == LD_DMA64 || loader == LD_DMA16; }
+constexpr bool is_gen(int loader) {
+  return loader == LD_DMA16 || loader == LD_SPLIT64G || loader == LD_SPLIT32G;
+}
 
 constexpr bool is_halo(int loader) { return loader == LD_HALO4 || loader == LD_HALO8; }
 
@@ -125,6 +134,9 @@ struct ConvArgs {
   // Ho), hTPI tiles per image (hG == 1), input patch hPH x hPW per image;
   // stores of rows that do not exist go to `sink` (32 int32)
   int hG, hTH, hTPI, hPH, hPW;
+  // C % 16 walks: 64 channels as filter rows, taps and channels, and in the input
+  int gen_r, gen_s, gen_c;
+  int64_t gen_step;
   // RGB8: 16-byte chunks (four taps) per filter row; four chunks as rows and chunks
   int rgb_chunks, rgb_step_r, rgb_step_c;
   int32_t* sink;
@@ -149,7 +161,14 @@ constexpr int conv_per_thread(int cfg) { return cfg == TC_256x128 ? 128 : 64; }
 // and 64-bit products of addressing every slab from its number took longer than
 // its MFMAs: 14x14x256 3x3 at batch 256 ran 56 -> 48 us plain, 74 -> 66 us
 // predicted).
-template <int BM, int BN, int WAVES = 4>
+//
+// GEN: any C % 16 == 0.  The depth is walked in order, and a slab's four chunks
+// may belong to different taps: each lane walks the taps of its own chunk (the
+// same in all its pieces), 64 channels on per slab, and chunks past the depth
+// take zero weights.  Against slabs staged through registers, plain / predicted:
+// 760 x 32 x 2000 in split tiles 31.9 / 38.7 -> 10.3 / 12.2 us, 50176 x 256 x 1296
+// in 128 x 128 tiles 49.5 / 53.7 -> 42.1 / 47.6.
+template <int BM, int BN, int WAVES = 4, bool GEN = false>
 struct RingLoad {
   static constexpr int AJ = BM / (16 * WAVES), BJ = BN / (16 * WAVES);
   static constexpr int kOps = AJ + BJ;  // loads per wave and slab
@@ -157,23 +176,23 @@ struct RingLoad {
   int aih[AJ], aiw[AJ];
   const int8_t* bsrc[BJ];
   int64_t padp, rowskip;
-  int ir, is, ic;  // next slab: filter tap, first channel
+  int ir, is, ic;  // next slab: filter tap, first channel (GEN: of the lane's chunk)
   int64_t atap;    // (ir * W + is) * C + ic
   int btap;        // (ir * S + is) * C + ic
+  int kt, kc;      // GEN: next slab of the tile, the lane's chunk
 
   __device__ inline void cols(const ConvArgs& a, int a_off, int n0, int wave, int lane) {
+    kc = ((lane & 3) ^ lds_swz(lane >> 2)) & 3;
 #pragma unroll
     for (int j = 0; j < BJ; ++j) {
       const int row = 16 * (WAVES * j + wave) + (lane >> 2);
       const int col = n0 + row;
       const int cc = col < a.K ? col : a.K - 1;
-      bsrc[j] = a.w + (int64_t)cc * a.wrow + (((lane & 3) ^ lds_swz(row)) & 3) * 16;
+      bsrc[j] = a.w + (int64_t)cc * a.wrow + (GEN ? 0 : kc * 16);
     }
     padp = (int64_t)(uintptr_t)&kPadVec[a_off];
     rowskip = (int64_t)(a.W - a.S) * a.C;
-    ir = is = ic = 0;
-    atap = 0;
-    btap = 0;
+    seek(a, 0);
   }
   // Rows m0 .. m0 + BM - 1, from their first slab.
   __device__ inline void rows(const ConvArgs& a, int m0, int wave, int lane) {
@@ -190,17 +209,26 @@ struct RingLoad {
       aiw[j] = ow * a.stride - a.pad;
       arow[j] = (int64_t)(uintptr_t)a.x +
                 (((int64_t)n * a.H + (oh * a.stride - a.pad)) * a.W + aiw[j]) * a.C +
-                (((lane & 3) ^ lds_swz(row)) & 3) * 16;
+                (GEN ? 0 : kc * 16);
     }
   }
   // The walk at slab q of a tile.
   __device__ inline void seek(const ConvArgs& a, int q) {
-    const int taps = a.R * a.S, chunk = q / taps, tap = q - chunk * taps;
-    ir = tap / a.S;
-    is = tap - ir * a.S;
-    ic = chunk * BK;
+    if constexpr (GEN) {
+      btap = q * BK + kc * 16;
+      const int tap = btap / a.C;
+      ic = btap - tap * a.C;
+      ir = tap / a.S;
+      is = tap - ir * a.S;
+      kt = q;
+    } else {
+      const int taps = a.R * a.S, chunk = q / taps, tap = q - chunk * taps;
+      ir = tap / a.S;
+      is = tap - ir * a.S;
+      ic = chunk * BK;
+      btap = tap * a.C + ic;
+    }
     atap = ((int64_t)ir * a.W + is) * a.C + ic;
-    btap = tap * a.C + ic;
   }
   // Issues load i (of kOps) of the next slab into stage (sa, sb).
   __device__ inline void load(const ConvArgs& a, int i, int8_t* sa, int8_t* sb, int wave) {
@@ -208,6 +236,9 @@ struct RingLoad {
       const bool ok = (unsigned)(aih[i] + ir) < (unsigned)a.H && (unsigned)(aiw[i] + is) < (unsigned)a.W;
       const int64_t p = ok ? arow[i] + atap : padp;
       dma16(reinterpret_cast<const int8_t*>(p), &sa[(WAVES * i + wave) * 1024]);
+    } else if constexpr (GEN) {
+      const int8_t* p = bsrc[i - AJ] + btap;
+      dma16(ir < a.R ? p : reinterpret_cast<const int8_t*>(&kPadVec[0]), &sb[(WAVES * (i - AJ) + wave) * 1024]);
     } else {
       dma16(bsrc[i - AJ] + btap, &sb[(WAVES * (i - AJ) + wave) * 1024]);
     }
@@ -215,6 +246,24 @@ struct RingLoad {
   // Steps to the slab after; true when that was the tile's last slab (the walk
   // is back at the first one).
   __device__ inline bool advance(const ConvArgs& a) {
+    if constexpr (GEN) {
+      if (++kt == (a.kdepth + BK - 1) / BK) {
+        seek(a, 0);
+        return true;
+      }
+      // 64 channels on: gen_r filter rows, gen_s taps, gen_c channels; a wrap of
+      // the channels moves one tap on, one of the taps a row
+      ic += a.gen_c;
+      const bool cw = ic >= a.C;
+      ic -= cw ? a.C : 0;
+      is += a.gen_s + (cw ? 1 : 0);
+      const bool sw = is >= a.S;
+      is -= sw ? a.S : 0;
+      ir += a.gen_r + (sw ? 1 : 0);
+      atap += a.gen_step + (sw ? rowskip : 0);
+      btap += BK;
+      return false;
+    }
     // next tap; after the last, the next channel chunk
     atap += a.C;
     btap += a.C;
@@ -483,10 +532,10 @@ template <int T>
 constexpr int kSplitStage = T * 64 * 64;  // bytes of a stage: 32 T rows, 32 T columns
 template <int T>
 constexpr int kSplitLds = 4 * (kSplitD + 1) * kSplitStage<T>;
-template <int T>
+template <int T, bool GEN>
 struct SplitTile {
   static constexpr int D = kSplitD, ST = kSplitStage<T>, SA = 32 * T * 64;
-  using Ring = RingLoad<32 * T, 32 * T, 1>;
+  using Ring = RingLoad<32 * T, 32 * T, 1, GEN>;
   static constexpr int OPS = Ring::kOps, MFMAS = 2 * T * T, PER = (OPS + MFMAS - 1) / MFMAS;
   Ring ld;
   int n;         // this wave's slabs

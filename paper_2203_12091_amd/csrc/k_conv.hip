@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
   constexpr int PER_THREAD = TM * TN * 16;
   // LDS slabs: two stages for the register-staged loaders; the ring of the
   // DMA loader is declared with it.
-  constexpr int NST = (LOADER == LD_DMA64 || SPLIT) ? 1 : 2;
+  constexpr int NST = (is_ring(LOADER) || SPLIT) ? 1 : 2;
   __shared__ __attribute__((aligned(16))) int8_t As[NST][SPLIT ? 16 : BM * 64];
   __shared__ __attribute__((aligned(16))) int8_t Bs[NST][SPLIT ? 16 : BN * 64];
   __shared__ int rs_tab[128];
@@ -144,15 +144,15 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 
   if constexpr (SPLIT != 0) {
     __shared__ __attribute__((aligned(16))) int8_t ring[kSplitLds<SPLIT>];
-    SplitTile<SPLIT> st;
+    SplitTile<SPLIT, is_gen(LOADER)> st;
     epi_loads();
     st.start(a, a_off, m0, n0, ktiles, wave, lane, ring);
     st.finish(a, wave, lane, ring, acc[0][0]);
-  } else if constexpr (LOADER == LD_DMA64) {
-    RingLoad<BM, BN> ld;
+  } else if constexpr (is_ring(LOADER)) {
+    RingLoad<BM, BN, 4, is_gen(LOADER)> ld;
     ld.cols(a, a_off, n0, wave, lane);
     ld.rows(a, m0, wave, lane);
-    constexpr int OPS = RingLoad<BM, BN>::kOps;
+    constexpr int OPS = decltype(ld)::kOps;
     constexpr int D = 2;                // slabs in flight (3: two blocks per CU instead of three, 30% slower)
     constexpr int ST = (BM + BN) * 64;  // bytes of a stage: rows, then columns
     __shared__ __attribute__((aligned(16))) int8_t stage[(D + 1) * ST];
@@ -479,17 +479,17 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 
 template <int BM, int BN, int TM, int TN, int MINW, int EPI>
 static void conv_dispatch_loader(int loader, dim3 grid, hipStream_t st, const ConvArgs& a) {
-  if (loader == LD_FAST64)
-    k_qconv<BM, BN, TM, TN, MINW, LD_FAST64, EPI><<<grid, 256, 0, st>>>(a);
-  else if (loader == LD_DMA64)
-    k_qconv<BM, BN, TM, TN, MINW, LD_DMA64, EPI><<<grid, 256, 0, st>>>(a);
-  else if (loader == LD_GEN16)
-    k_qconv<BM, BN, TM, TN, MINW, LD_GEN16, EPI><<<grid, 256, 0, st>>>(a);
-  else if (loader == LD_HALO4 || loader == LD_HALO8 || split_t(loader) != 0)
-    return;  // these tiles have their own configurations
-  else if constexpr (EPI == EPI_ACC && BN == 64) {
-    if (loader == LD_RGB8) k_qconv<BM, BN, TM, TN, MINW, LD_RGB8, EPI><<<grid, 256, 0, st>>>(a);
-    else k_qconv<BM, BN, TM, TN, MINW, LD_RGB4, EPI><<<grid, 256, 0, st>>>(a);
+  // (256 x 64 tiles take the staged loaders, the others the ring)
+  if constexpr (BN == 64) {
+    if (loader == LD_FAST64) k_qconv<BM, BN, TM, TN, MINW, LD_FAST64, EPI><<<grid, 256, 0, st>>>(a);
+    else if (loader == LD_GEN16) k_qconv<BM, BN, TM, TN, MINW, LD_GEN16, EPI><<<grid, 256, 0, st>>>(a);
+    else if constexpr (EPI == EPI_ACC) {
+      if (loader == LD_RGB8) k_qconv<BM, BN, TM, TN, MINW, LD_RGB8, EPI><<<grid, 256, 0, st>>>(a);
+      else k_qconv<BM, BN, TM, TN, MINW, LD_RGB4, EPI><<<grid, 256, 0, st>>>(a);
+    }
+  } else {
+    if (loader == LD_DMA64) k_qconv<BM, BN, TM, TN, MINW, LD_DMA64, EPI><<<grid, 256, 0, st>>>(a);
+    else k_qconv<BM, BN, TM, TN, MINW, LD_DMA16, EPI><<<grid, 256, 0, st>>>(a);
   }
 }
 
@@ -561,8 +561,13 @@ dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t
   else if (wide_ok && loader == LD_FAST64 && a.kdepth >= 512 && 2 * tiles_256x128 >= 3 * (int64_t)cus)
     cfg = TC_256x128;
   else cfg = TC_128x128;
-  // channel multiples of 64 outside the narrow tiles: slabs through the LDS ring
-  if (loader == LD_FAST64 && cfg != TC_256x64) loader = LD_DMA64;
+  // outside the narrow tiles: slabs through the LDS ring
+  if (cfg != TC_256x64) loader = loader == LD_FAST64 ? LD_DMA64 : LD_DMA16;
+  // (64 channels = gen_r S + gen_s taps and gen_c channels)
+  a.gen_r = BK / d.c / d.s;
+  a.gen_s = BK / d.c % d.s;
+  a.gen_c = BK % d.c;
+  a.gen_step = ((int64_t)a.gen_r * d.w + a.gen_s) * d.c + a.gen_c;
   // 3x3 filters over small images with 256-channel multiples, on request:
   // halo tiles of whole output rows (224 rows in 7 MFMA row tiles, else 128
   // in 4) when the patch fits 512 LDS rows and, first choice, the tiles fill
@@ -618,13 +623,14 @@ dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t
 //   25088 x 64 x 256   11.5 17.2 / 13.8 16.2 / --         (392 of 64)
 //   10816 x 384 x 1728 18.7 26.4 / 32.3 36.6 / --         (1014 of 64)
 void split_setup(ConvArgs& a, int& loader, int& cfg, dim3& grid, int cus) {
-  if (loader != LD_FAST64 && loader != LD_DMA64) return;
+  if (loader != LD_FAST64 && loader != LD_DMA64 && loader != LD_GEN16 && loader != LD_DMA16) return;
   auto tiles = [&](int t) { return (int64_t)((a.M + t - 1) / t) * ((a.K + t - 1) / t); };
   int t;
   if (tiles(32) <= 2 * cus) t = 32;
   else if (tiles(64) <= cus) t = 64;
   else return;
-  loader = t == 32 ? LD_SPLIT32 : LD_SPLIT64;
+  if (loader == LD_GEN16 || loader == LD_DMA16) loader = t == 32 ? LD_SPLIT32G : LD_SPLIT64G;
+  else loader = t == 32 ? LD_SPLIT32 : LD_SPLIT64;
   cfg = t == 32 ? TC_32x32 : TC_64x64;
   grid = dim3((a.M + t - 1) / t, (a.K + t - 1) / t);
 }
@@ -633,11 +639,13 @@ template <int EPI>
 static void conv_run(const ConvArgs& a, int loader, int cfg, dim3 grid, hipStream_t st) {
   if constexpr (EPI == EPI_ACC) {
     if (cfg == TC_64x64) {
-      k_qconv<64, 64, 1, 1, 1, LD_SPLIT64, EPI><<<grid, 256, 0, st>>>(a);
+      if (loader == LD_SPLIT64) k_qconv<64, 64, 1, 1, 1, LD_SPLIT64, EPI><<<grid, 256, 0, st>>>(a);
+      else k_qconv<64, 64, 1, 1, 1, LD_SPLIT64G, EPI><<<grid, 256, 0, st>>>(a);
       return;
     }
     if (cfg == TC_32x32) {
-      k_qconv<32, 32, 1, 1, 1, LD_SPLIT32, EPI><<<grid, 256, 0, st>>>(a);
+      if (loader == LD_SPLIT32) k_qconv<32, 32, 1, 1, 1, LD_SPLIT32, EPI><<<grid, 256, 0, st>>>(a);
+      else k_qconv<32, 32, 1, 1, 1, LD_SPLIT32G, EPI><<<grid, 256, 0, st>>>(a);
       return;
     }
     if (cfg == TC_H224x256) {

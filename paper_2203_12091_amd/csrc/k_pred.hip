@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   // bound on the values per thread and tile (one for all tile shapes, so that
   // the decision does not depend on the shape)
   constexpr int PER_THREAD = 64;
-  constexpr int NST = (LOADER == LD_DMA64) ? 3 : 2;  // LDS stages
+  constexpr int NST = is_ring(LOADER) ? 3 : 2;  // LDS stages
   constexpr int SA = BM * 64, SB = BN * 64;
   __shared__ __attribute__((aligned(16))) int8_t stage[SPLIT ? kSplitLds<SPLIT> : NST * (SA + SB)];
   __shared__ int rs_tab[128];
@@ -84,8 +84,8 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   // small grids the set-up and the waits for the channel constants and the
   // first slabs, one after the other, took 3.5 of a call's 9 us).
   using Load = std::conditional_t<
-      SPLIT != 0, SplitTile<SPLIT == 0 ? 1 : SPLIT>,
-      std::conditional_t<LOADER == LD_DMA64, RingLoad<BM, BN>, StagedLoad<BM, BN, LOADER>>>;
+      SPLIT != 0, SplitTile<SPLIT == 0 ? 1 : SPLIT, is_gen(LOADER)>,
+      std::conditional_t<is_ring(LOADER), RingLoad<BM, BN, 4, is_gen(LOADER)>, StagedLoad<BM, BN, LOADER>>>;
   Load ld;
   int ti = tm0;  // tile being loaded
   bool ended = false;
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   };
   if constexpr (SPLIT != 0) {
     ld.start(a, a_off, tm0 * BM, n0, ktiles, wave, lane, stage);
-  } else if constexpr (LOADER == LD_DMA64) {
+  } else if constexpr (is_ring(LOADER)) {
     ld.cols(a, a_off, n0, wave, lane);
     ld.rows(a, tm0 * BM, wave, lane);
     for (int i = 0; i < D && i < total; ++i) issue(ld, stage + i * ST);
@@ -158,8 +158,10 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
     epi_channel_raw(ep, eu, eraw[ni], Mx[ni], Ax[ni]);
-    Mx[ni] = ldexp(Mx[ni], ex);
-    Ax[ni] = ldexp(Ax[ni], ex);
+    // columns past the tensor's hold zeros, which add nothing to any sum
+    const bool in = n0 + wn * WCOLS + ni * 32 + (lane & 31) < a.K;
+    Mx[ni] = in ? ldexp(Mx[ni], ex) : 0.0;
+    Ax[ni] = in ? ldexp(Ax[ni], ex) : 0.0;
   }
   // Sums over the block's tiles.  One tile's sums of x q are exact in fp64 (the
   // bound of the window's set-up) and then added as integers.
@@ -181,11 +183,15 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   const int qj = lane & 3;
   const unsigned s1 = (qj & 1) ? 0x03070105u : 0x06020400u;
   const unsigned s2 = (qj & 2) ? 0x03020706u : 0x05040100u;
-  // full tiles store through a buffer descriptor: row offsets in scalars
+  // tiles of BM rows store through a buffer descriptor: row offsets in scalars,
+  // columns past the tensor's dropped by its range (their tiles took the general
+  // form before: 401408 x 96 x 16 83 -> 52 us)
   int vo[TN];
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni)
-    vo[ni] = (4 * (lane >> 5) + qj) * a.K + n0 + wn * WCOLS + ni * 32 + ((lane & 31) & ~3);
+    vo[ni] = n0 + wn * WCOLS + ni * 32 + ((lane & 31) & ~3) < a.K
+                 ? (4 * (lane >> 5) + qj) * a.K + n0 + wn * WCOLS + ni * 32 + ((lane & 31) & ~3)
+                 : INT_MIN;  // past the descriptor's range: dropped
 
   // The codes leave as dwords: a lane holds one column at 4 consecutive rows
   // (e = 4g .. 4g + 3), and a 4 x 4 byte transpose inside each lane quad (one
@@ -207,7 +213,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     wq[1] += exact_i64(wa.PL[1] * up);
   };
 
-  // A full tile of a window whose first candidate does not saturate: its
+  // A tile of BM rows of a window whose first candidate does not saturate: its
   // values' min / max, its window sums and the codes of candidate PJ as bytes
   // (q - 128 when unsigned).  NN: no negative values.  Straight-line code.
   auto tile_full = [&](int m0, auto nn, auto pj_) __attribute__((always_inline)) {
@@ -273,7 +279,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     wa.A[PJ] += (double)dq;
     add_tile();
   };
-  // Any other tile: values past the tensor's rows or columns add nothing, both
+  // Any other tile: values past the tensor's rows add nothing, both
   // candidates' codes are clamped in fp64 (a first candidate that saturates: x
   // is not bounded by the codes' range; or an unsigned format forced on
   // negative values), or only the min / max (no window).  A rolled loop over
@@ -364,7 +370,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     const int m0 = tm * BM;
     using F = std::false_type;
     using T = std::true_type;
-    if (fast && m0 + BM <= a.M && n0 + BN <= a.K) {
+    if (fast && m0 + BM <= a.M) {
       if (var) {
         if (pj) tile_full(m0, T(), T());
         else tile_full(m0, T(), F());
@@ -390,7 +396,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
       for (int e = 0; e < 4 * NG; ++e) acc[0][0][e] += 128 * csum[0];
       (void)finish_tile(tm);
     }
-  } else if constexpr (LOADER == LD_DMA64) {
+  } else if constexpr (is_ring(LOADER)) {
     // Slab s of the block's sequence sits in stage s % NST; at step s the loads
     // of slab s have landed, those of s + 1 .. s + D - 1 and, issued at the
     // step, s + D are in flight, across tile ends too.  vmcnt counts in order
@@ -398,7 +404,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     // of the next slabs and the stores of the tiles that ended within the last
     // D steps (`ends`, bit i: a full tile ended at step s - 1 - i; a partial
     // tile's stores are not counted, which only waits longer).
-    constexpr int OPS = RingLoad<BM, BN>::kOps, STORES = TM * TN * 4;
+    constexpr int OPS = Load::kOps, STORES = TM * TN * 4;
     static_assert(D <= 3 && OPS * (D - 1) + D * STORES < 64, "vmcnt range");
     int8_t* cur = stage;
     int s = 0;
@@ -489,7 +495,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   double mn = INFINITY, mx = -INFINITY;
 #pragma unroll
   for (int ni = 0; ni < TN; ++ni) {
-    if (lo[ni] > hi[ni]) continue;  // no in-range value in this column
+    if (lo[ni] > hi[ni] || n0 + wn * WCOLS + ni * 32 + (lane & 31) >= a.K) continue;  // no value
     double Mc, Ac;
     epi_channel(ep, eu, n0 + wn * WCOLS + ni * 32 + (lane & 31), Mc, Ac);
     const double f0 = fmax(fma((double)lo[ni], Mc, Ac), relo);
@@ -559,21 +565,17 @@ hipError_t launch_conv_pred(const Ctx& c, const fxpq_conv_desc& d, const void* x
   a.flags = c.sc.flags;
   bool timed = timer_begin(c, FXPQ_TIMER_CBLOCK_PRED);
   rgb8_setup(c, d, a, loader);
-  if (cfg == TC_64x64) {
-    pred_run<64, 64, LD_SPLIT64>(c, a);
-  } else if (cfg == TC_32x32) {
-    pred_run<32, 32, LD_SPLIT32>(c, a);
-  } else if (cfg == TC_256x64) {
-    switch (loader) {
-      case LD_FAST64: pred_run<256, 64, LD_FAST64>(c, a); break;
-      case LD_GEN16: pred_run<256, 64, LD_GEN16>(c, a); break;
-      case LD_RGB8: pred_run<256, 64, LD_RGB8>(c, a); break;
-      default: pred_run<256, 64, LD_RGB4>(c, a); break;
-    }
-  } else if (loader == LD_DMA64) {
-    pred_run<128, 128, LD_DMA64>(c, a);
-  } else {
-    pred_run<128, 128, LD_GEN16>(c, a);
+  switch (loader) {
+    case LD_SPLIT64: pred_run<64, 64, LD_SPLIT64>(c, a); break;
+    case LD_SPLIT64G: pred_run<64, 64, LD_SPLIT64G>(c, a); break;
+    case LD_SPLIT32: pred_run<32, 32, LD_SPLIT32>(c, a); break;
+    case LD_SPLIT32G: pred_run<32, 32, LD_SPLIT32G>(c, a); break;
+    case LD_FAST64: pred_run<256, 64, LD_FAST64>(c, a); break;
+    case LD_GEN16: pred_run<256, 64, LD_GEN16>(c, a); break;
+    case LD_RGB8: pred_run<256, 64, LD_RGB8>(c, a); break;
+    case LD_RGB4: pred_run<256, 64, LD_RGB4>(c, a); break;
+    case LD_DMA64: pred_run<128, 128, LD_DMA64>(c, a); break;
+    default: pred_run<128, 128, LD_DMA16>(c, a); break;
   }
   timer_end(c, timed, 2.0 * (double)a.M * (double)d.k * (double)(d.r * d.s * d.c));
   hipError_t e = hipGetLastError();

@@ -19,9 +19,12 @@ CASES = [
     (3, 192, 84, 85, 512, 1, 1, 0, True, False),    # three
     (3, 64, 84, 85, 512, 3, 1, 1, False, True),     # nine, filter taps
     (3, 64, 84, 85, 452, 1, 1, 0, False, False),    # ragged columns
+    (3, 16, 84, 85, 512, 3, 1, 1, True, True),      # ring, C % 16: four taps a slab
+    (3, 48, 84, 85, 452, 3, 1, 1, False, False),    # slabs across taps, ragged columns
+    (3, 80, 84, 85, 512, 1, 1, 0, False, True),     # a ragged second slab
     (5, 64, 165, 163, 64, 1, 1, 0, True, True),     # 64 columns, staged slabs
     (5, 16, 165, 163, 64, 3, 1, 1, False, False),   # C % 16
-    (21, 32, 57, 57, 100, 1, 1, 0, True, False),    # C % 16, 128 columns, ragged
+    (21, 32, 57, 57, 100, 1, 1, 0, True, False),    # ring, C % 16, half a slab, ragged
     (11, 3, 223, 221, 64, 7, 2, 3, False, False),   # padded RGB, 16-byte pixels
     (11, 3, 223, 221, 32, 11, 2, 5, True, True),    # padded RGB, three chunks per filter row
     (3, 3, 50, 47, 64, 3, 1, 1, False, True),       # one chunk

@@ -25,6 +25,14 @@ CASES = [
     (1, 64, 60, 60, 132, 3, 1, 1, True, True),      # 64 x 64, nine taps, ragged columns
     (1, 64, 128, 128, 64, 1, 1, 0, False, False),   # 256 tiles of 64 x 64
     (1, 64, 128, 129, 64, 1, 1, 0, False, True),    # past them
+    # channels a multiple of 16 only: chunks of one slab in several taps
+    (1, 16, 3, 5, 4, 1, 1, 0, True, False),         # a quarter of a slab
+    (2, 16, 9, 7, 40, 3, 1, 1, False, True),        # four taps a slab, a ragged last slab
+    (1, 48, 13, 11, 36, 5, 1, 2, True, False),      # slabs across taps and filter rows
+    (3, 80, 10, 9, 96, 3, 2, 1, False, False),      # strided
+    (1, 112, 8, 8, 64, 1, 1, 0, True, True),        # one tap, a ragged second slab
+    (1, 32, 128, 65, 64, 3, 1, 1, False, True),     # 64 x 64 tiles
+    (1, 48, 60, 60, 132, 2, 1, 0, True, False),     # 64 x 64, ragged both ways
 ]
 
 
