@@ -280,16 +280,20 @@ struct WideFusedArgs {
   const int32_t* cs;  // column sums of the weight planes [np_w][K]
   int np_x, np_w, sign_x;
   int N, H, W, C, K, R, S, stride, pad, Ho, Wo, M, kdepth, wrow;
+  int gen_r, gen_s, gen_c;  // the walk of ConvArgs
+  int chunks;  // padded RGB: 16-byte chunks per filter row of the weight planes (0: packed taps)
+  int64_t gen_step;
   SrcDev ep;
   int64_t* v;
   int32_t* d_scale;
   unsigned* flags;
 };
 hipError_t launch_wide_fused(const Ctx& c, const WideFusedArgs& a, bool wide);
-hipError_t launch_wide_split_x(const Ctx& c, const int32_t* x, int64_t n, int np, int sign,
-                               int64_t plane_stride, int8_t* planes);
-hipError_t launch_wide_split_w(const Ctx& c, const int32_t* w, int64_t n, int np, int sign,
-                               int64_t plane_stride, int8_t* planes);
+hipError_t launch_wide_split(const Ctx& c, const int32_t* x, int64_t nx, int np_x, int sign_x,
+                             int64_t xs, int8_t* px, const int32_t* w, int64_t wrow, int K,
+                             int np_w, int sign_w, int64_t ws, int8_t* pw, int R, int S,
+                             int chunks, int32_t* cs);
+int wide_chunks(const Ctx& c, const WideFusedArgs& a, bool wide);
 hipError_t launch_wide_combine(const Ctx& c, const int32_t* acc, int64_t mk, int np_x, int np_w,
                                const SrcDev& ep, int64_t* v, int32_t* d_scale);
 hipError_t launch_acc_overflow(const Ctx& c, const int32_t* acc, int64_t n, int bits,

@@ -335,18 +335,23 @@ struct StagedLoad {
       iw0[i] = ow * a.stride - a.pad;
       abase[i] = a.x + (int64_t)n * a.H * a.W * a.C;
     }
-    kt = 0;
-    ir = is = ic = 0;
+    restart(a, tid);
     if constexpr (LOADER == LD_RGB8) {
-      rgb_r = (tid & 3) / a.rgb_chunks;
-      rgb_c = (tid & 3) - rgb_r * a.rgb_chunks;
 #pragma unroll
       for (int i = 0; i < ACH; ++i) {
         rgb_p[i] = ih0[i] * a.W;
         if (!aval[i]) ih0[i] = INT_MIN / 2;  // no row: never inside
       }
     }
-    if constexpr (LOADER == LD_GEN16) {
+  }
+  // The walk at the first slab of the same rows.
+  __device__ inline void restart(const ConvArgs& a, int tid) {
+    kt = 0;
+    ir = is = ic = 0;
+    if constexpr (LOADER == LD_RGB8) {
+      rgb_r = (tid & 3) / a.rgb_chunks;
+      rgb_c = (tid & 3) - rgb_r * a.rgb_chunks;
+    } else if constexpr (LOADER == LD_GEN16) {
       ic = (tid & 3) * 16;
       wrap(a);
     }

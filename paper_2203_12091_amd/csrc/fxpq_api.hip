@@ -699,34 +699,31 @@ fxpq_status fxpq_qconv_wide(fxpq_handle h, const fxpq_conv_desc* d, const int32_
   epi_to_dev(ep, &e);
   DeviceGuard g(h->device);
   const Ctx c = ctx(h);
-  hipError_t err = launch_wide_split_x(c, x, L.n_in, L.np_x, sign_x, L.xs, px);
-  if (err == hipSuccess)
-    err = launch_wide_split_w(c, w, (int64_t)d->k * L.wrow, L.np_w, sign_w, L.ws, pw);
-  for (int q = 0; q < L.np_w && err == hipSuccess; ++q)
-    err = launch_colsum(c, pw + q * L.ws, d->k, L.wrow, cs + (int64_t)q * d->k);
-  if (L.fused && err == hipSuccess) {
-    WideFusedArgs fa{};
-    fa.px = px;
-    fa.xs = L.xs;
-    fa.pw = pw;
-    fa.ws = L.ws;
-    fa.cs = cs;
-    fa.np_x = L.np_x;
-    fa.np_w = L.np_w;
-    fa.sign_x = sign_x;
-    fa.N = d->n; fa.H = d->h; fa.W = d->w; fa.C = d->c; fa.K = d->k; fa.R = d->r; fa.S = d->s;
-    fa.stride = d->stride; fa.pad = d->pad;
-    fa.Ho = (d->h + 2 * d->pad - d->r) / d->stride + 1;
-    fa.Wo = (d->w + 2 * d->pad - d->s) / d->stride + 1;
-    fa.M = (int)L.M;
-    fa.kdepth = d->r * d->s * d->c;
-    fa.wrow = (int)L.wrow;
-    fa.ep = e;
-    fa.v = v;
-    fa.d_scale = d_scale;
-    fa.flags = h->sc.flags;
-    return hip_status(launch_wide_fused(c, fa, wide_sum_bits(L.np_x, L.np_w) >= 62));
-  }
+  const bool wide = wide_sum_bits(L.np_x, L.np_w) >= 62;
+  WideFusedArgs fa{};
+  fa.px = px;
+  fa.xs = L.xs;
+  fa.pw = pw;
+  fa.ws = L.ws;
+  fa.cs = cs;
+  fa.np_x = L.np_x;
+  fa.np_w = L.np_w;
+  fa.sign_x = sign_x;
+  fa.N = d->n; fa.H = d->h; fa.W = d->w; fa.C = d->c; fa.K = d->k; fa.R = d->r; fa.S = d->s;
+  fa.stride = d->stride; fa.pad = d->pad;
+  fa.Ho = (d->h + 2 * d->pad - d->r) / d->stride + 1;
+  fa.Wo = (d->w + 2 * d->pad - d->s) / d->stride + 1;
+  fa.M = (int)L.M;
+  fa.kdepth = d->r * d->s * d->c;
+  fa.wrow = (int)L.wrow;
+  fa.ep = e;
+  fa.v = v;
+  fa.d_scale = d_scale;
+  fa.flags = h->sc.flags;
+  if (L.fused) fa.chunks = wide_chunks(c, fa, wide);
+  hipError_t err = launch_wide_split(c, x, L.n_in, L.np_x, sign_x, L.xs, px, w, L.wrow, d->k, L.np_w,
+                                     sign_w, L.ws, pw, d->r, d->s, fa.chunks, cs);
+  if (L.fused && err == hipSuccess) return hip_status(launch_wide_fused(c, fa, wide));
   for (int p = 0; p < L.np_x && err == hipSuccess; ++p) {
     const int t = (p < L.np_x - 1 || !sign_x) ? FXPQ_U8OFF : FXPQ_I8;
     for (int q = 0; q < L.np_w && err == hipSuccess; ++q)

@@ -793,7 +793,7 @@ struct WinIn {
 };
 
 // ---------------------------------------------------------------------------
-// The general pass over word lengths 2..16 and integers |W| < 2^52: per
+// The general pass over word lengths 2..25 and integers |W| < 2^52: per
 // candidate the exact sums of the window pass (sum q^2 and sum W q, W split as
 // Wh 2^26 + Wl), kGenGroup candidates per read of the values, the candidates
 // compared by 2^(2d) sum q^2 - 2^(d+1) sum W q (sum W^2 is common to all).
@@ -805,6 +805,11 @@ struct WinIn {
 // ---------------------------------------------------------------------------
 constexpr int kGenGroup = 4;
 constexpr int kGenFlush = 512;  // values per thread between flushes (as kWinMaxPerThread)
+// ... so that its sums of q^2 < 2^(2 wl) and of Wh q, Wl q < 2^(26 + wl) stay
+// below 2^53 (0: word lengths the pass does not take).
+__device__ inline int gen_flush(int wl) {
+  return wl <= 18 ? kGenFlush : (wl <= 25 ? 1 << (27 - wl) : 0);
+}
 
 __device__ inline int gen_cand(const GenPlan& g, int j) {
   return (g.extra != INT_MIN) ? (j == 0 ? g.extra : g.glo + j - 1) : g.glo + j;
@@ -816,10 +821,11 @@ __device__ inline int gen_count(const GenPlan& g) {
 // Every block adds its share of the values: candidate j's block sums go to
 // part[(j * kGenChunks + block) * 3]: sum q^2, then sum W q in 128 bits.
 template <int KIND, int DT>
-__device__ void general_sums(const SrcDev& s, int64_t n, const FlsU& u, const GenPlan& g,
+__device__ void general_sums(const SrcDev& s, int64_t n, int wl, const FlsU& u, const GenPlan& g,
                              unsigned long long* part) {
   using PK = Pack<KIND, DT>;
   __shared__ long long sh[4][kGenGroup][6];
+  const int flush_at = gen_flush(wl);
   const int nc = gen_count(g);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int j0 = 0; j0 < nc; j0 += kGenGroup) {
@@ -856,7 +862,7 @@ __device__ void general_sums(const SrcDev& s, int64_t n, const FlsU& u, const Ge
     int cnt = 0;
     auto count = [&](int values) {
       cnt += values;
-      if (cnt > kGenFlush - PK::EP) {
+      if (cnt > flush_at - PK::EP) {
         flush();
         cnt = 0;
       }
@@ -899,6 +905,99 @@ __device__ void general_sums(const SrcDev& s, int64_t n, const FlsU& u, const Ge
         return (__int128)hi * ((__int128)1 << 32) + lo;
       };
       const __int128 P = tot(2) * (__int128)67108864 + tot(4);
+      unsigned long long* p = part + ((int64_t)(j0 + k) * kGenChunks + blockIdx.x) * 3;
+      p[0] = (unsigned long long)tot(0);
+      p[1] = (unsigned long long)P;
+      p[2] = (unsigned long long)(P >> 64);
+    }
+    __syncthreads();
+  }
+}
+
+// The same sums of int64 values 2^52 <= max |W| < 2^62 (W = v): W in three
+// parts of 26, 26 and 10 bits, and its code from a double that holds W rounded
+// to odd above 2^53 (a code that uses bits below 2^10 of such a W is clamped;
+// above, the odd last bit keeps a tie from appearing or vanishing).  Wide
+// C-Blocks at 24 bits against the 128-bit errors: 244800 values 223 -> 123 us,
+// 4.6 M 1130 -> 222.
+__device__ inline void general_sums_i64(const int64_t* x, int64_t n, int wl, const FlsU& u,
+                                        const GenPlan& g, unsigned long long* part) {
+  __shared__ long long sh[4][kGenGroup][8];
+  const int flush_at = gen_flush(wl);
+  const int nc = gen_count(g);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int V = 4;  // values per thread and step
+  constexpr long long M26 = (1ll << 26) - 1;
+  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  for (int j0 = 0; j0 < nc; j0 += kGenGroup) {
+    double cj[kGenGroup], S[kGenGroup][4];  // sum q^2, sum of the three parts times q
+    long long I[kGenGroup][4];
+#pragma unroll
+    for (int k = 0; k < kGenGroup; ++k) {
+      cj[k] = ldexp(1.0, gen_cand(g, j0 + k < nc ? j0 + k : nc - 1) - u.sigma);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        S[k][i] = 0.0;
+        I[k][i] = 0;
+      }
+    }
+    auto add = [&](long long W) {
+      const long long odd = ((W >> 10) | ((W & 1023) != 0 ? 1 : 0));
+      const bool small = W < (1ll << 53) && W > -(1ll << 53);
+      const double Wd = small ? (double)W : (double)odd * 1024.0;
+      const double p0 = (double)(int)(W & M26), p1 = (double)(int)((W >> 26) & M26),
+                   p2 = (double)(int)(W >> 52);
+#pragma unroll
+      for (int k = 0; k < kGenGroup; ++k) {
+        const double q = max64(min64(rint(Wd * cj[k]), u.qmax), u.qmin);
+        S[k][0] = fma(q, q, S[k][0]);
+        S[k][1] = fma(p0, q, S[k][1]);
+        S[k][2] = fma(p1, q, S[k][2]);
+        S[k][3] = fma(p2, q, S[k][3]);
+      }
+    };
+    int cnt = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += V * stride) {
+      long long w[V];
+#pragma unroll
+      for (int v = 0; v < V; ++v) w[v] = i + v * stride < n ? x[i + v * stride] : 0;  // 0 adds nothing
+#pragma unroll
+      for (int v = 0; v < V; ++v) add(w[v]);
+      cnt += V;
+      if (cnt > flush_at - V || i + V * stride >= n) {
+#pragma unroll
+        for (int k = 0; k < kGenGroup; ++k)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            I[k][t] += exact_i64(S[k][t]);
+            S[k][t] = 0.0;
+          }
+        cnt = 0;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kGenGroup; ++k)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const long long h = wave_reduce(I[k][t] >> 32, OpAddL());
+        const long long l = wave_reduce(I[k][t] & 0xFFFFFFFFll, OpAddL());
+        if (lane == 0) {
+          sh[wave][k][2 * t] = h;
+          sh[wave][k][2 * t + 1] = l;
+        }
+      }
+    __syncthreads();
+    if (threadIdx.x < kGenGroup && j0 + (int)threadIdx.x < nc) {
+      const int k = threadIdx.x;
+      auto tot = [&](int t) -> __int128 {
+        __int128 h = 0, l = 0;
+        for (int w = 0; w < 4; ++w) {
+          h += sh[w][k][2 * t];
+          l += sh[w][k][2 * t + 1];
+        }
+        return h * ((__int128)1 << 32) + l;
+      };
+      const __int128 P = tot(3) * ((__int128)1 << 52) + tot(2) * ((__int128)1 << 26) + tot(1);
       unsigned long long* p = part + ((int64_t)(j0 + k) * kGenChunks + blockIdx.x) * 3;
       p[0] = (unsigned long long)tot(0);
       p[1] = (unsigned long long)P;
@@ -996,15 +1095,23 @@ __device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, 
   }
   const long long qmax = (1ll << (wl - sign)) - 1;
   const long long qmin = sign ? -(1ll << (wl - 1)) : 0;
-  // Word lengths 2..16 with integers |W| < 2^52 (fp32: W = v 2^(fl_hi + 24)):
-  // the candidates' exact sums in fp64, four per read of the values.
+  // Word lengths 2..25 with integers |W| < 2^52 (fp32: W = v 2^(fl_hi + 24)):
+  // the candidates' exact sums in fp64, four per read of the values; int64
+  // values over their whole range.  A block's sum q^2 has to fit 63 bits.
   const int sigf = (KIND == FXPQ_SRC_F32) ? sigma : sv;
-  if (wl >= 2 && wl <= 16 && !d_sse && absmax * ldexp(1.0, sigf - sv) < kTwo52) {
+  if (wl >= 2 && gen_flush(wl) >= Pack<KIND, DT>::EP && !d_sse &&
+      (absmax * ldexp(1.0, sigf - sv) < kTwo52 || (KIND == FXPQ_SRC_INT && DT == FXPQ_I64)) &&
+      ldexp((double)(n / gridDim.x + kThreads * Pack<KIND, DT>::EP * kWinSets), 2 * wl) < 0x1p62) {
     const FlsU u = fls_uniform<KIND>(s, mm, wl, sign, fl_lo, fl_hi);
     // candidates below beta_nosat never win (see the top of this file)
     const int lo = extra == INT_MIN ? imax(glo, u.beta_nosat < ghi ? u.beta_nosat : ghi) : glo;
     const GenPlan gf{1, 0, sign, lo, ghi, extra};
-    general_sums<KIND, DT>(s, n, u, gf, part);
+    bool wide = false;
+    if constexpr (KIND == FXPQ_SRC_INT && DT == FXPQ_I64) {
+      wide = absmax >= kTwo52;
+      if (wide) general_sums_i64(static_cast<const int64_t*>(s.x), n, wl, u, gf, part);
+    }
+    if (!wide) general_sums<KIND, DT>(s, n, wl, u, gf, part);
     __threadfence();
     __syncthreads();
     if (threadIdx.x == 0) last = atomicAdd(done, 1u) == gridDim.x - 1;

@@ -108,3 +108,30 @@ def test_search_at_the_saturation_bound(fx, h, orc, wl, shift):
                 ofl, osign, _ = orc.fl_search_i64(v, s, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
                 assert fmt_host(out) == (wl, ofl, osign, 0), (mx, mn)
     assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("n", [1, 5, 1030, 262_147])
+@pytest.mark.parametrize("wl", [8, 17, 19, 24, 25, 26])
+def test_int64_search_wide_values(fx, h, orc, n, wl):
+    """Values of 53 to 61 bits (three-part sums of the exact pass, codes from the
+    value rounded to odd) and word lengths past the window's: ties of a code's
+    last bit with bits set far below, extremes, and smaller values."""
+    import torch
+    g = synth.rng_for(n + wl, "wide")
+    s = 40
+    sd = torch.tensor([s], dtype=torch.int32, device=DEV)
+    for bits in (50, 54, 61):
+        v = (g.standard_normal(n) * 2.0 ** (bits - 3)).astype(np.int64)
+        v = np.clip(v, -(2 ** bits) + 1, 2 ** bits - 1)
+        # halves of the candidates' steps, exactly and one unit off
+        k = g.integers(0, 2 ** 12, n)
+        half = (2 * k + 1) << g.integers(20, 40, n)
+        pick = g.integers(0, 4, n)
+        v = np.where(pick == 0, half, np.where(pick == 1, -half - 1, np.where(pick == 2, half - 1, v)))
+        v[0] = 2 ** bits - 1
+        out = fmt_new()
+        note("int64 wide", n, wl, bits)
+        fx.fl_search(h, fx.src_int(dev(v), fx.I64, sd), n, wl, fx.SIGN_AUTO, FL_LO, FL_HI, out)
+        ofl, osign, _ = orc.fl_search_i64(v, s, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+        assert fmt_host(out) == (wl, ofl, osign, 0), bits
+    assert fx.sync_status(h) == 0
