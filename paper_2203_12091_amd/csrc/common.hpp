@@ -271,7 +271,7 @@ hipError_t launch_preprocess(const Ctx& c, const SrcDev& s, const double* d_minm
 hipError_t launch_colsum(const Ctx& c, const int8_t* w, int64_t k, int64_t len, int32_t* out);
 // Wide C-Blocks (k_wide.hip): digit planes of int32 codes, and the exact
 // combination of the plane contractions with the epilogue.
-// One fused wide C-Block contraction (see k_wide_fused).
+// One fused wide C-Block contraction (see k_wide_split, k_wide_tile).
 struct WideFusedArgs {
   const int8_t* px;   // np_x input byte planes (NHWC), plane stride xs
   int64_t xs;

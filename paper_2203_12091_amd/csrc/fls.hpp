@@ -148,6 +148,7 @@ struct WinSetup {
   FlsU u;
   int verdict;  // 0: run window; 1: done (fl_hi); 2: general for all; 3: failure
   int b0, b1, nc, bce;
+  int split;    // sums of W q in two parts
 };
 
 // Decisions every block of a window pass (and its finalize) takes from the
@@ -183,6 +184,18 @@ __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, 
   w.b1 = (w.b0 + kWindow - 1 < fl_hi) ? w.b0 + kWindow - 1 : fl_hi;
   w.nc = w.b1 - w.b0 + 1;
   w.bce = (w.b1 < fl_hi) ? w.b1 + 1 : w.b1;
+  w.split = SPLIT;
+  if constexpr (KIND == FXPQ_SRC_F32) {
+    // fp32 values in units of 2^-(b1 + 24): an integer wherever a window code is
+    // not 0 (|v| >= 2^-(b1 + 1), 24-bit mantissa).  Small word lengths need no
+    // split then: W < 2^(wl + 25)
+    const int s2 = w.b1 + 24;
+    if (w.verdict == 0 && ldexp(w.u.absmax, s2) * qabs * (double)per_thread < kTwo53) {
+      w.split = 0;
+      w.u.sigma = s2;
+      w.u.wscale = ldexp(1.0, s2);
+    }
+  }
   return w;
 }
 
@@ -275,6 +288,64 @@ template <bool SPLIT, bool NONNEG, bool CLAMP0, int NB = 1>
 __device__ inline void win_consume(const WinCtx& c, WinAcc& acc, double W) {
   double q[kWindow];
   win_consume<SPLIT, NONNEG, CLAMP0, NB>(c, acc, W, q);
+}
+
+// The unsplit form in units of the first candidate's step: x = W 2^(b0 -
+// sigma), its code rne(x), the second candidate's rne(2 x), and the clipping
+// errors against the bounds' ranges scaled to x, so that no bound needs its own
+// product.  The sums of x q, x^2 and the clipping errors are those of the plain
+// form times exact powers of two (win_acc_unscale).  17 fp64 operations per
+// value with one bound, 29 with four (25 and 49 in the split form): searches of
+// 38.5 M fp32 values at 8 bits 47 -> 38 us (the read takes 33), 12.8 M at 6 bits
+// with four bounds 32 -> 24, int32 28 -> 24.
+struct WinX {
+  double xs;  // v -> x
+  double qmin, qmax, hi[kCeBounds], lo[kCeBounds];
+};
+__device__ inline WinX win_x(const FlsU& u, const WinSetup& ws) {
+  WinX c;
+  c.xs = ldexp(u.wscale, ws.b0 - u.sigma);
+  c.qmin = u.qmin;
+  c.qmax = u.qmax;
+#pragma unroll
+  for (int k = 0; k < kCeBounds; ++k) {
+    c.hi[k] = ldexp(u.qmax, ws.b0 - ws.bce - k);
+    c.lo[k] = ldexp(u.qmin, ws.b0 - ws.bce - k);
+  }
+  return c;
+}
+template <bool NONNEG, bool CLAMP0, int NB>
+__device__ inline void win_consume_x(const WinX& c, WinAcc& acc, double x, double (&q)[kWindow]) {
+  static_assert(kWindow == 2, "two window candidates");
+  acc.V2 = fma(x, x, acc.V2);
+  q[0] = rint(x);
+  if (CLAMP0) {
+    q[0] = min64(q[0], c.qmax);
+    if (!NONNEG) q[0] = max64(q[0], c.qmin);
+  }
+  q[1] = min64(rint(x + x), c.qmax);
+  if (!NONNEG) q[1] = max64(q[1], c.qmin);
+#pragma unroll
+  for (int j = 0; j < kWindow; ++j) {
+    acc.A[j] = fma(q[j], q[j], acc.A[j]);
+    acc.PL[j] = fma(x, q[j], acc.PL[j]);
+  }
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    double r = min64(x, c.hi[k]);
+    if (!NONNEG) r = max64(r, c.lo[k]);
+    const double e = x - r;
+    acc.CE[k] = fma(e, e, acc.CE[k]);
+  }
+}
+template <int NB>
+__device__ inline void win_acc_unscale(const FlsU& u, const WinSetup& ws, WinAcc& acc) {
+  const int up = u.sigma - ws.b0;
+#pragma unroll
+  for (int j = 0; j < kWindow; ++j) acc.PL[j] = ldexp(acc.PL[j], up);
+  acc.V2 = ldexp(acc.V2, 2 * up);
+#pragma unroll
+  for (int k = 0; k < NB; ++k) acc.CE[k] = ldexp(acc.CE[k], 2 * (ws.bce + k - ws.b0));
 }
 
 // Window candidate whose codes a predicted FxP-QLayer writes: the second

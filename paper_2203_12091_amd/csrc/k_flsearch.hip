@@ -22,6 +22,8 @@
 // Pass 2 ("general", only when pass 1 could not decide, when the caller asks
 //   for every error, or for word lengths above 16): the exact error of every
 //   remaining candidate in 128-bit integer arithmetic, compared exactly.
+#include <type_traits>
+
 #include "fls.hpp"
 
 namespace fxpq {
@@ -55,19 +57,25 @@ __device__ inline void store_codes(int8_t* y, int64_t i, const int* c, unsigned 
 
 // Main loop of the streaming window pass over this thread's values.
 // MM: also the min / max of the values (predicted FxP-QLayer) into mn / mx.
-template <int KIND, int DT, bool NONNEG, bool CLAMP0, int NB, bool CODES, bool MM = false>
+template <int KIND, int DT, bool SPLIT, bool NONNEG, bool CLAMP0, int NB, bool CODES, bool MM>
 __device__ inline void win_loop(const SrcDev& s, int64_t n, const FlsU& u, const WinSetup& ws,
-                                const WinCodes& wcd, WinAcc& acc, double* mn = nullptr,
-                                double* mx = nullptr) {
-  const WinCtx wc = win_ctx(u, ws);
+                                const WinCodes& wcd, WinAcc& acc, double* mn, double* mx) {
+  WinCtx wc;
+  WinX wx;
+  if constexpr (SPLIT) wc = win_ctx(u, ws);
+  else wx = win_x(u, ws);
   win_acc_zero(acc);
   double lo = INFINITY, hi = -INFINITY;
+  const double post = u.wscale;
   // Codes of one value: the window's codes are clamped except candidate 0
   // when it cannot saturate (beta_nosat), where a value at qmax + 1/2 rounds
   // to qmax + 1 (same error either way, but the code must be clamped).
-  auto consume = [&](double W, int* cq) {
+  auto consume = [&](double v, int* cq) {
     double q[kWindow];
-    win_consume<win_split(KIND, DT), NONNEG, CLAMP0, NB>(wc, acc, W, q);
+    // integer sources are searched at sigma = sv (W = v); fp32 values are
+    // scaled, exactly
+    if constexpr (SPLIT) win_consume<true, NONNEG, CLAMP0, NB>(wc, acc, KIND == FXPQ_SRC_F32 ? v * post : v, q);
+    else win_consume_x<NONNEG, CLAMP0, NB>(wx, acc, v * wx.xs, q);
     if constexpr (CODES) {
 #pragma unroll
       for (int j = 0; j < kWindow; ++j) cq[j] = (int)q[j];
@@ -79,9 +87,6 @@ __device__ inline void win_loop(const SrcDev& s, int64_t n, const FlsU& u, const
   const int64_t gtid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   ThreadVals<PK::V> tv;
   thread_vals_init<KIND, DT>(s, (int64_t)blockIdx.x * kThreads * PK::V, tv);
-  // Integer sources are searched at sigma = sv (W = v); fp32 values are
-  // scaled by 2^(sigma - sv) = 2^(fl_hi + 24), exactly.
-  const double post = u.wscale;
   const int64_t nfull = n - n % PK::EP;
   // backwards: the pass starts with the lines the previous kernel (the
   // conv, or the eltwise min / max pass, which reads forwards) touched last
@@ -93,7 +98,7 @@ __device__ inline void win_loop(const SrcDev& s, int64_t n, const FlsU& u, const
         lo = min64(lo, v[j]);
         hi = max64(hi, v[j]);
       }
-      consume(KIND == FXPQ_SRC_F32 ? v[j] * post : v[j], cq[j]);
+      consume(v[j], cq[j]);
     }
     if constexpr (CODES) {
 #pragma unroll
@@ -114,16 +119,45 @@ __device__ inline void win_loop(const SrcDev& s, int64_t n, const FlsU& u, const
         lo = min64(lo, vi);
         hi = max64(hi, vi);
       }
-      consume(vi * u.wscale, cq);
+      consume(vi, cq);
       if constexpr (CODES) {
 #pragma unroll
         for (int k = 0; k < kWindow; ++k)
           if (wcd.y[k]) wcd.y[k][i] = (int8_t)((cq[k] & 0xFF) ^ (wcd.xorw & 0xFF));
       }
     }
+  if constexpr (!SPLIT) win_acc_unscale<NB>(u, ws, acc);
   if constexpr (MM) {
     *mn = lo;
     *mx = hi;
+  }
+}
+// The variant of the min / max and of the split, then the block's partial sums.
+template <int KIND, int DT, int NB, bool CODES, bool MM = false>
+__device__ __forceinline__ void win_pass(const SrcDev& s, int64_t n, const WinSetup& ws,
+                                         const double* mm, const WinCodes& wcd, int64_t bid,
+                                         long long* part_i, double* part_f, WinShared& wsh,
+                                         double* mn = nullptr, double* mx = nullptr) {
+  const FlsU& u = ws.u;
+  WinAcc acc;
+  auto run = [&](auto split) __attribute__((always_inline)) {
+    constexpr bool SP = decltype(split)::value;
+    switch (win_variant(u, ws, mm)) {
+      case 0: win_loop<KIND, DT, SP, false, false, NB, CODES, MM>(s, n, u, ws, wcd, acc, mn, mx); break;
+      case 1: win_loop<KIND, DT, SP, false, true, NB, CODES, MM>(s, n, u, ws, wcd, acc, mn, mx); break;
+      case 2: win_loop<KIND, DT, SP, true, false, NB, CODES, MM>(s, n, u, ws, wcd, acc, mn, mx); break;
+      default: win_loop<KIND, DT, SP, true, true, NB, CODES, MM>(s, n, u, ws, wcd, acc, mn, mx); break;
+    }
+    if constexpr (SP) win_write_partials(acc, NB, bid, part_i, part_f, wsh);
+    else win_write_partials_int(acc, NB, bid, part_i, part_f, wsh);
+  };
+  if constexpr (KIND == FXPQ_SRC_F32) {
+    if (ws.split) run(std::true_type());
+    else run(std::false_type());
+  } else if constexpr (win_split(KIND, DT)) {
+    run(std::true_type());
+  } else {
+    run(std::false_type());
   }
 }
 
@@ -383,9 +417,9 @@ __global__ __launch_bounds__(kThreads) void k_fls_window(
     wcd.qmax = (int)u.qmax;
     wcd.xorw = u.sign ? 0u : 0x80808080u;
   }
-  WinAcc acc;
   if constexpr (KIND == FXPQ_SRC_ADD) {
     // eltwise sums through the histogram when it applies (uniform)
+    WinAcc acc;
     __shared__ unsigned hist[kAddHistBins];
     const AddHist ap = add_hist_setup(s, u, ws, per_thread);
     if (ap.ok) {
@@ -395,14 +429,7 @@ __global__ __launch_bounds__(kThreads) void k_fls_window(
       return;
     }
   }
-  switch (win_variant(u, ws, mm)) {
-    case 0: win_loop<KIND, DT, false, false, NB, CODES>(s, n, u, ws, wcd, acc); break;
-    case 1: win_loop<KIND, DT, false, true, NB, CODES>(s, n, u, ws, wcd, acc); break;
-    case 2: win_loop<KIND, DT, true, false, NB, CODES>(s, n, u, ws, wcd, acc); break;
-    default: win_loop<KIND, DT, true, true, NB, CODES>(s, n, u, ws, wcd, acc); break;
-  }
-  if constexpr (win_split(KIND, DT)) win_write_partials(acc, NB, blockIdx.x, part_i, part_f, wsh);
-  else win_write_partials_int(acc, NB, blockIdx.x, part_i, part_f, wsh);
+  win_pass<KIND, DT, NB, CODES>(s, n, ws, mm, wcd, blockIdx.x, part_i, part_f, wsh);
 }
 
 // Predicted FxP-QLayer over a streaming source: the window of the min / max
@@ -443,15 +470,7 @@ __global__ __launch_bounds__(kThreads) void k_qlayer_pred(
     wcd.y[pj] = y;
     wcd.qmax = (int)u.qmax;
     wcd.xorw = u.sign ? 0u : 0x80808080u;
-    WinAcc acc;
-    switch (win_variant(u, ws, mm)) {
-      case 0: win_loop<KIND, DT, false, false, NB, true, true>(s, n, u, ws, wcd, acc, &mn, &mx); break;
-      case 1: win_loop<KIND, DT, false, true, NB, true, true>(s, n, u, ws, wcd, acc, &mn, &mx); break;
-      case 2: win_loop<KIND, DT, true, false, NB, true, true>(s, n, u, ws, wcd, acc, &mn, &mx); break;
-      default: win_loop<KIND, DT, true, true, NB, true, true>(s, n, u, ws, wcd, acc, &mn, &mx); break;
-    }
-    if constexpr (KIND == FXPQ_SRC_F32) win_write_partials(acc, NB, blockIdx.x, part_i, part_f, wsh);
-    else win_write_partials_int(acc, NB, blockIdx.x, part_i, part_f, wsh);
+    win_pass<KIND, DT, NB, true, true>(s, n, ws, mm, wcd, blockIdx.x, part_i, part_f, wsh, &mn, &mx);
   } else {
     using PK = Pack<KIND, DT>;
     ThreadVals<PK::V> tv;
@@ -1298,16 +1317,7 @@ __global__ __launch_bounds__(kThreads) void k_search_small(
                       plan->gen_extra};
     }
   } else {
-    WinAcc acc;
-    const WinCodes wcd{};
-    switch (win_variant(ws.u, ws, mm)) {
-      case 0: win_loop<KIND, DT, false, false, NB, false>(s, n, ws.u, ws, wcd, acc); break;
-      case 1: win_loop<KIND, DT, false, true, NB, false>(s, n, ws.u, ws, wcd, acc); break;
-      case 2: win_loop<KIND, DT, true, false, NB, false>(s, n, ws.u, ws, wcd, acc); break;
-      default: win_loop<KIND, DT, true, true, NB, false>(s, n, ws.u, ws, wcd, acc); break;
-    }
-    if constexpr (win_split(KIND, DT)) win_write_partials(acc, NB, 0, slot_i, slot_f, wsh);
-    else win_write_partials_int(acc, NB, 0, slot_i, slot_f, wsh);
+    win_pass<KIND, DT, NB, false>(s, n, ws, mm, WinCodes{}, 0, slot_i, slot_f, wsh);
     __syncthreads();
     if (threadIdx.x < 64) {
       const WinResult r = win_decide(ws, NB, fl_hi, slot_i, slot_f);
