@@ -142,10 +142,11 @@ struct ConvArgs {
   int32_t* sink;
 };
 
-// Tile configurations: block BM x BN, four waves of (32 TM) x (32 TN), MINW
+// Tile configurations: block BM x BN, four waves of (32 TM) x (32 TN) (32 x 64 in
+// 128 x 64 tiles), MINW
 // waves per SIMD requested from the register allocator.
 enum TileCfg { TC_256x64 = 0, TC_128x128 = 1, TC_256x128 = 2, TC_H224x256 = 3, TC_H128x256 = 4,
-               TC_64x64 = 5, TC_32x32 = 6 };
+               TC_64x64 = 5, TC_32x32 = 6, TC_128x64 = 7 };
 
 // Accumulators per thread of a configuration (the per-thread bound of the
 // fused window epilogue).

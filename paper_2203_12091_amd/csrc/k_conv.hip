@@ -622,13 +622,25 @@ dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t
 //   6272 x 128 x 1152  13.2 20.1 / 10.7 15.3 / 14.0 19.2  (784)
 //   25088 x 64 x 256   11.5 17.2 / 13.8 16.2 / --         (392 of 64)
 //   10816 x 384 x 1728 18.7 26.4 / 32.3 36.6 / --         (1014 of 64)
+// Between the two, 128 x 64 tiles where 128 x 128 ones take at most two thirds of
+// the CUs: 6272 x 256 x 2304 (98 tiles of 128 x 128) 19.0 22.9 -> 15.7 20.3, 3136 x
+// 512 x 4608 (100) 28.7 34.6 -> 23.6 28.5, 10816 x 256 x 2304 (170) 21.3 25.6 ->
+// 19.5 24.0, 12544 x 256 x 2304 (196) 19.7 24.1 -> 20.6 24.6.  (Two groups of four
+// waves on half the depth each in one 128 x 128 tile gave nothing: a slab's LDS
+// traffic is what a CU waits for.)
 void split_setup(ConvArgs& a, int& loader, int& cfg, dim3& grid, int cus) {
   if (loader != LD_FAST64 && loader != LD_DMA64 && loader != LD_GEN16 && loader != LD_DMA16) return;
   auto tiles = [&](int t) { return (int64_t)((a.M + t - 1) / t) * ((a.K + t - 1) / t); };
   int t;
   if (tiles(32) <= 2 * cus) t = 32;
   else if (tiles(64) <= cus) t = 64;
-  else return;
+  else {
+    if (cfg == TC_128x128 && 3 * tiles(128) <= 2 * cus) {
+      cfg = TC_128x64;
+      grid = dim3((a.M + 127) / 128, (a.K + 63) / 64);
+    }
+    return;
+  }
   if (loader == LD_GEN16 || loader == LD_DMA16) loader = t == 32 ? LD_SPLIT32G : LD_SPLIT64G;
   else loader = t == 32 ? LD_SPLIT32 : LD_SPLIT64;
   cfg = t == 32 ? TC_32x32 : TC_64x64;
@@ -638,6 +650,11 @@ void split_setup(ConvArgs& a, int& loader, int& cfg, dim3& grid, int cus) {
 template <int EPI>
 static void conv_run(const ConvArgs& a, int loader, int cfg, dim3 grid, hipStream_t st) {
   if constexpr (EPI == EPI_ACC) {
+    if (cfg == TC_128x64) {
+      if (loader == LD_DMA64) k_qconv<128, 64, 1, 2, 3, LD_DMA64, EPI><<<grid, 256, 0, st>>>(a);
+      else k_qconv<128, 64, 1, 2, 3, LD_DMA16, EPI><<<grid, 256, 0, st>>>(a);
+      return;
+    }
     if (cfg == TC_64x64) {
       if (loader == LD_SPLIT64) k_qconv<64, 64, 1, 1, 1, LD_SPLIT64, EPI><<<grid, 256, 0, st>>>(a);
       else k_qconv<64, 64, 1, 1, 1, LD_SPLIT64G, EPI><<<grid, 256, 0, st>>>(a);

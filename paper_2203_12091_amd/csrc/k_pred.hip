@@ -31,7 +31,7 @@ __device__ inline double uniform(double v) {
 template <int BM, int BN, int LOADER>
 __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   constexpr int SPLIT = split_t(LOADER);
-  constexpr int TM = SPLIT ? 1 : 2, TN = TM;  // MFMA tiles per wave
+  constexpr int TM = SPLIT ? 1 : BM * BN / 8192, TN = SPLIT ? 1 : 2;  // MFMA tiles per wave
   constexpr int NG = SPLIT == 1 ? 1 : 4;      // groups of four accumulators per thread and tile
   constexpr int WROWS = 8 * NG * TM, WCOLS = 32 * TN;
   constexpr int WGN = BN / WCOLS;  // waves along N
@@ -574,8 +574,14 @@ hipError_t launch_conv_pred(const Ctx& c, const fxpq_conv_desc& d, const void* x
     case LD_GEN16: pred_run<256, 64, LD_GEN16>(c, a); break;
     case LD_RGB8: pred_run<256, 64, LD_RGB8>(c, a); break;
     case LD_RGB4: pred_run<256, 64, LD_RGB4>(c, a); break;
-    case LD_DMA64: pred_run<128, 128, LD_DMA64>(c, a); break;
-    default: pred_run<128, 128, LD_DMA16>(c, a); break;
+    case LD_DMA64:
+      if (cfg == TC_128x64) pred_run<128, 64, LD_DMA64>(c, a);
+      else pred_run<128, 128, LD_DMA64>(c, a);
+      break;
+    default:
+      if (cfg == TC_128x64) pred_run<128, 64, LD_DMA16>(c, a);
+      else pred_run<128, 128, LD_DMA16>(c, a);
+      break;
   }
   timer_end(c, timed, 2.0 * (double)a.M * (double)d.k * (double)(d.r * d.s * d.c));
   hipError_t e = hipGetLastError();

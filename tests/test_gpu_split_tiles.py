@@ -25,6 +25,9 @@ CASES = [
     (1, 64, 60, 60, 132, 3, 1, 1, True, True),      # 64 x 64, nine taps, ragged columns
     (1, 64, 128, 128, 64, 1, 1, 0, False, False),   # 256 tiles of 64 x 64
     (1, 64, 128, 129, 64, 1, 1, 0, False, True),    # past them
+    # 128 x 64 tiles
+    (1, 64, 90, 91, 136, 3, 1, 1, False, True),
+    (1, 48, 127, 65, 132, 1, 1, 0, True, False),
     # channels a multiple of 16 only: chunks of one slab in several taps
     (1, 16, 3, 5, 4, 1, 1, 0, True, False),         # a quarter of a slab
     (2, 16, 9, 7, 40, 3, 1, 1, False, True),        # four taps a slab, a ragged last slab
