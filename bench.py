@@ -45,7 +45,7 @@ ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 PRED_OPS_PER_VALUE = 22
 BATCH, IMAGE = 256, 224
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cblock_predicted_resnet50_b256_traffic.md")
-WINDOW_SOURCES = ["k_conv.hip", "fls.hpp", "values.hpp", "common.hpp"]
+WINDOW_SOURCES = ["k_pred.hip", "conv_load.hpp", "fls.hpp", "values.hpp", "common.hpp"]
 
 
 def parse():
