@@ -92,7 +92,7 @@ def committed_traffic():
 
 
 def host_info():
-    """The GPU machine's host as the oracle sees it: CPU model, logical CPUs, the
+    """The host as the oracle sees it: CPU model, logical CPUs, the
     threads the oracle's OpenMP regions use, compiler and flags."""
     import subprocess
     from oracle import build as ob
@@ -772,7 +772,7 @@ def main():
                    "timed_forwards_rerun": timed_misses},
         "roofline": {"bound": "alu", "achieved": round(pr_alu, 2), "peak": round(ALU_PEAK_TOPS, 2),
                      "unit": "TOP/s", "frac": round(pr_alu / ALU_PEAK_TOPS, 4), "traffic": traffic,
-                     "kernel": "k_qconv predicted C-Block (conv + epilogue + FL-search window + codes)",
+                     "kernel": "k_cblock_pred: predicted C-Block (conv + epilogue + FL-search window + codes)",
                      "launches": pr_n, "avg_launch_ms": round(pr_ms / max(pr_n, 1), 5),
                      "algorithmic_ops_per_launch": round(PRED_OPS_PER_VALUE * pr_vals / max(pr_n, 1)),
                      "ops_per_output_value": PRED_OPS_PER_VALUE, "ms_per_forward": round(pr_ms, 3),

@@ -6,10 +6,12 @@
 //   columns j = output channel       N = K
 //   depth   k = (r, s, c), c fastest K = R * S * C
 //
-// A block computes a BM x BN tile with 4 waves of 64 x 64 (2 x 2 MFMA tiles),
-// stepping through depth in 64-byte slabs staged in LDS (double buffered, the
-// next slab's global loads in flight during the current slab's MFMAs).  No
-// im2col buffer: each thread gathers its rows' 16-byte chunks straight from
+// A block computes a BM x BN tile with 4 waves (64 x 64 each, 2 x 2 MFMA tiles,
+// at 128 x 128), stepping through depth in 64-byte slabs staged in LDS (a ring
+// of three filled by LDS-DMA, or two stages through registers, the next slabs'
+// loads in flight during the current slab's MFMAs); for grids that leave CUs
+// idle the four waves share one small tile and split its depth (split_setup).
+// No im2col buffer: each thread gathers its rows' 16-byte chunks straight from
 // the NHWC tensor, with zero padding (code 0, or -128 for codes stored as
 // u - 128, both meaning the value 0).
 //
