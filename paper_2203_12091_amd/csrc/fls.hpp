@@ -188,12 +188,16 @@ __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, 
   if constexpr (KIND == FXPQ_SRC_F32) {
     // fp32 values in units of 2^-(b1 + 24): an integer wherever a window code is
     // not 0 (|v| >= 2^-(b1 + 1), 24-bit mantissa).  Small word lengths need no
-    // split then: W < 2^(wl + 25)
-    const int s2 = w.b1 + 24;
-    if (w.verdict == 0 && ldexp(w.u.absmax, s2) * qabs * (double)per_thread < kTwo53) {
+    // split then: where the first candidate does not saturate, |W| <= (qabs + 1)
+    // 2^(b1 - b0 + 24).  The rule looks at the window alone, not at the values'
+    // magnitude: a predicted call forms its sums with the previous min / max and
+    // decides with this call's, and both have to choose the same units wherever
+    // they agree on the window.
+    if (w.verdict == 0 && w.b0 == w.u.beta_nosat &&
+        ldexp((qabs + 1.0) * qabs * (double)per_thread, w.b1 - w.b0 + 24) < kTwo53) {
       w.split = 0;
-      w.u.sigma = s2;
-      w.u.wscale = ldexp(1.0, s2);
+      w.u.sigma = w.b1 + 24;
+      w.u.wscale = ldexp(1.0, w.u.sigma);
     }
   }
   return w;

@@ -667,14 +667,13 @@ __global__ __launch_bounds__(kFinThreads) void k_fls_window_fin(
 // combines the min / max keys of the slots into this call's exact min / max
 // and checks that the window the pass evaluated (from the predicted min / max
 // held in mm) is this call's window: same verdict 0, candidates, clipping
-// bound, sign and variant.  Then the wave decides from the window sums; the
-// format is recorded when the decision is final and is the candidate whose
-// codes the pass wrote, else *miss is set.  mm ends with this call's
-// min / max; the other slot set is cleared for the next search.
-// The decision itself, by one wave.  deferred: the calls that consumed this
-// call's codes have already run with the format held in *out (the
-// prediction), so a hit also needs the decision to be that format; the
-// slots are the call's own set, cleared afterwards for its next use.
+// bound, sign, variant and units of the sums.  Then the wave decides from the
+// window sums; the format is recorded when the decision is final and is the
+// candidate whose codes the pass wrote, else *miss is set.  mm ends with this
+// call's min / max.  deferred: the calls that consumed this call's codes have
+// already run with the format held in *out (the prediction), so a hit also
+// needs the decision to be that format; the slots are the call's own set,
+// cleared afterwards for its next use.
 template <int KIND>
 __device__ inline void pred_decision(const SrcDev& s, int wl, int sign_req, int fl_lo, int fl_hi,
                                      int nce, int64_t per_thread, double* mm,
@@ -689,6 +688,7 @@ __device__ inline void pred_decision(const SrcDev& s, int wl, int sign_req, int 
   const WinSetup wa = win_setup<KIND>(s, act, wl, sign_req, fl_lo, fl_hi, MODE_SEARCH, per_thread);
   const bool same = wp.verdict == 0 && wa.verdict == 0 && wp.b0 == wa.b0 && wp.b1 == wa.b1 &&
                     wp.nc == wa.nc && wp.bce == wa.bce && wp.u.sign == wa.u.sign &&
+                    wp.split == wa.split && wp.u.sigma == wa.u.sigma &&
                     win_variant(wp.u, wp, pred) == win_variant(wa.u, wa, act);
   const fxpq_fmt used = *out;
   bool hit = false, undecided = false;
@@ -713,14 +713,8 @@ __device__ inline void pred_decision(const SrcDev& s, int wl, int sign_req, int 
   }
 }
 
-// Decision of a predicted C-Block or FxP-QLayer (one wave, after the pass):
-// combines the min / max keys of the slots into this call's exact min / max
-// and checks that the window the pass evaluated (from the predicted min / max
-// held in mm) is this call's window: same verdict 0, candidates, clipping
-// bound, sign and variant.  Then the wave decides from the window sums; the
-// format is recorded when the decision is final and is the candidate whose
-// codes the pass wrote, else *miss is set.  mm ends with this call's
-// min / max; the other slot set is cleared for the next search.
+// The decision right after the pass (one wave); the other slot set is cleared
+// for the next search.
 template <int KIND>
 __global__ __launch_bounds__(kFinThreads) void k_pred_fin(
     SrcDev s, int wl, int sign_req, int fl_lo, int fl_hi, int nce, int64_t per_thread, double* mm,

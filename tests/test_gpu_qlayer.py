@@ -322,3 +322,43 @@ def test_qlayer_predicted_eltwise_forms(fx, h, orc, form):
             cases += 1
     assert hits >= cases // 2, (hits, cases)
     check_flags(fx, h)
+
+
+@pytest.mark.parametrize("defer", [False, True])
+@pytest.mark.parametrize("n", [4096, 32768])
+def test_qlayer_predicted_f32_saturating_range(fx, h, orc, n, defer):
+    """fp32 values that saturate at the lowest fl: the window is the same
+    whatever their magnitude, so a prediction from smaller or larger extremes
+    stands, and its sums must be combined in the units they were formed in.
+    Extremes 2^k / 1.05 and 1.05 2^k predict each other."""
+    import torch
+    lo, hi, wl = 0, 8, 8
+    bulk = (synth.normal(71, "qlsat", (n,), std=1.0) * np.float32(40.0)).astype(np.float32)
+    for k in range(10, 19):
+        for small in (True, False):
+            ext = np.float32(2.0 ** k / 1.05 if small else 2.0 ** k * 1.05)
+            pred = 2.0 ** k * 1.05 if small else 2.0 ** k / 1.05
+            x = bulk.copy()
+            x[5], x[n - 9] = ext, -ext
+            fl, sign, _ = orc.fl_search_f32(x, wl, fx.SIGN_AUTO, lo, hi)
+            assert fl in (lo, lo + 1) and sign == 1
+            want = orc.quantize_f32(x, wl, fl, sign)
+            src = fx.src_f32(dev(x))
+            for entry in (lo, lo + 1):
+                note("qlayer predicted saturating", n, defer, k, small, entry)
+                out = fmt_dev(wl, entry, 1)
+                mm = torch.tensor([-pred, pred], dtype=torch.float64, device=DEV)
+                miss = torch.zeros(1, dtype=torch.int32, device=DEV)
+                codes = empty((n,), torch.int8)
+                fx.predicted_defer(h, defer)
+                fx.qlayer_predicted(h, src, n, wl, fx.SIGN_AUTO, lo, hi, out, codes, fx.C8, mm, miss)
+                if defer:
+                    fx.predicted_decide(h)
+                    fx.predicted_defer(h, False)
+                assert tuple(host(mm)) == (float(-ext), float(ext))
+                # the clipping error of the extremes alone excludes every higher fl: the window decides
+                assert int(host(miss)[0]) == (0 if entry == fl else 1), (k, small, entry, fl)
+                if entry == fl:
+                    assert fmt_host(out) == (wl, fl, sign, 0)
+                    assert np.array_equal(host(codes).astype(np.int64), want)
+    check_flags(fx, h)
