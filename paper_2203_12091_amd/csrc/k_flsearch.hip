@@ -1116,8 +1116,10 @@ __device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, 
       (absmax * ldexp(1.0, sigf - sv) < kTwo52 || (KIND == FXPQ_SRC_INT && DT == FXPQ_I64)) &&
       ldexp((double)(n / gridDim.x + kThreads * Pack<KIND, DT>::EP * kWinSets), 2 * wl) < 0x1p62) {
     const FlsU u = fls_uniform<KIND>(s, mm, wl, sign, fl_lo, fl_hi);
-    // candidates below beta_nosat never win (see the top of this file)
-    const int lo = extra == INT_MIN ? imax(glo, u.beta_nosat < ghi ? u.beta_nosat : ghi) : glo;
+    // candidates below beta_nosat never win (see the top of this file); int64
+    // extremes from 2^53 on come rounded to fp64, so it may be one too high
+    const int nosat = u.beta_nosat - (KIND == FXPQ_SRC_INT && DT == FXPQ_I64 && absmax >= kTwo53 ? 1 : 0);
+    const int lo = extra == INT_MIN ? imax(glo, nosat < ghi ? nosat : ghi) : glo;
     const GenPlan gf{1, 0, sign, lo, ghi, extra};
     bool wide = false;
     if constexpr (KIND == FXPQ_SRC_INT && DT == FXPQ_I64) {

@@ -135,3 +135,24 @@ def test_int64_search_wide_values(fx, h, orc, n, wl):
         ofl, osign, _ = orc.fl_search_i64(v, s, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
         assert fmt_host(out) == (wl, ofl, osign, 0), bits
     assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("n", [1, 9001])
+@pytest.mark.parametrize("wl", [2, 4, 8, 16])
+def test_int64_extreme_rounded_to_the_bound(fx, h, orc, n, wl):
+    """A largest value one unit above (qmax + 1/2) 2^k, which fp64 rounds onto
+    that bound: it saturates there, and one fl lower its error is smaller."""
+    import torch
+    for sign in (0, 1):
+        for k in range(53 - wl + sign, 60 - wl + sign):
+            s = k + 4  # the bound at fl 3
+            sd = torch.tensor([s], dtype=torch.int32, device=DEV)
+            for du in (-1, 0, 1):
+                v = np.zeros(n, np.int64)
+                v[n // 2] = ((2 ** (wl - sign) * 2 - 1) << k) + du
+                out = fmt_new()
+                note("int64 bound", n, wl, sign, k, du)
+                fx.fl_search(h, fx.src_int(dev(v), fx.I64, sd), n, wl, sign, FL_LO, FL_HI, out)
+                ofl, osign, _ = orc.fl_search_i64(v, s, wl, sign, FL_LO, FL_HI)
+                assert fmt_host(out) == (wl, ofl, osign, 0), (sign, k, du)
+    assert fx.sync_status(h) == 0
