@@ -513,7 +513,8 @@ __global__ void k_rgb8_weights(const int8_t* w, int K, int R, int S, int wrow, i
 // 96.8 (two chunks per filter row -> one); 256 x 224 x 224, 7x7 stride 2 204.5 /
 // 274.8 -> 194.2 / 263.9 (addresses from the image row instead of 64-bit products).
 void rgb8_setup(const Ctx& c, const fxpq_conv_desc& d, ConvArgs& a, int& loader) {
-  if (loader != LD_RGB4 || d.w < 4 || !c.sc.rgb_w) return;
+  // (the loader's pixel indices within an image are 32-bit)
+  if (loader != LD_RGB4 || d.w < 4 || (int64_t)d.h * d.w > INT_MAX || !c.sc.rgb_w) return;
   const int chunks = (d.s + 3) / 4;
   const int64_t wrow8 = ((int64_t)d.r * chunks * 16 + 63) / 64 * 64;
   if (d.k * wrow8 > (int64_t)kRgbWBytes) return;

@@ -770,7 +770,10 @@ static bool wide_split_tiles(const Ctx& c, const WideFusedArgs& a, bool wide) {
 
 int wide_chunks(const Ctx& c, const WideFusedArgs& a, bool wide) {
   const int chunks = (a.S + 3) / 4;
-  if (a.C != 4 || a.W < 4 || wide_split_tiles(c, a, wide) || a.R * chunks * 16 > a.wrow) return 0;
+  // (LD_RGB8's pixel indices within an image are 32-bit)
+  if (a.C != 4 || a.W < 4 || (int64_t)a.H * a.W > INT_MAX || wide_split_tiles(c, a, wide) ||
+      a.R * chunks * 16 > a.wrow)
+    return 0;
   return chunks;
 }
 
