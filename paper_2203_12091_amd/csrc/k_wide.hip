@@ -308,6 +308,15 @@ __device__ inline ConvArgs conv_args(const WideFusedArgs& a) {
   return c;
 }
 
+// A tap of the packed padded RGB filters: its filter row and column, and its
+// byte offset from tap (0, 0)'s pixel.  Past the last tap: never inside an image
+// (no row or column index, INT_MIN / 2 for a missing row among them, plus
+// INT_MIN / 2 is one of an image that has as many rows and columns).
+struct alignas(16) RgbTap {
+  int r, s;
+  int64_t off;
+};
+
 // Slabs of C % 16 == 0 inputs: the ring of the 8-bit contraction, moved from
 // plane pair to plane pair.
 struct WideRing {
@@ -336,7 +345,7 @@ struct WideRing {
     }
   }
   __device__ inline void start(const WideFusedArgs& a, const PairWalk& first, int kt, int n, int m0,
-                               int n0, int lane, int8_t* lds, const int2*) {
+                               int n0, int lane, int8_t* lds, const RgbTap*) {
     ca = conv_args(a);
     at = first;
     left = n;
@@ -385,13 +394,13 @@ struct WideRgb {
   int ih0[PC], iw0[PC];
   v4i ra[PC], rb[PC];
   int8_t* ring;
-  const int2* tab;
+  const RgbTap* tab;
   int st;
 
   __device__ inline void gload(const WideFusedArgs& a, int lane) {
     const int kc = lane & 3, padw = at.off(a) ? (int)0x80808080 : 0;
     const int64_t px = at.p * a.xs;
-    int2 tp[4];
+    RgbTap tp[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) tp[e] = tab[kt * 16 + kc * 4 + e];
 #pragma unroll
@@ -399,10 +408,10 @@ struct WideRgb {
       bool ok[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        ok[e] = (unsigned)(ih0[i] + (tp[e].x >> 16)) < (unsigned)a.H &&
-                (unsigned)(iw0[i] + (tp[e].x & 0xFFFF)) < (unsigned)a.W;
+        ok[e] = (unsigned)(ih0[i] + tp[e].r) < (unsigned)a.H &&
+                (unsigned)(iw0[i] + tp[e].s) < (unsigned)a.W;
         // (a readable address where the tap is outside: loads without branches)
-        const int8_t* ad = xb[i] + px + tp[e].y;
+        const int8_t* ad = xb[i] + px + tp[e].off;
         ra[i][e] = *reinterpret_cast<const int*>(ok[e] ? ad : a.px);
       }
 #pragma unroll
@@ -425,7 +434,7 @@ struct WideRgb {
     }
   }
   __device__ inline void start(const WideFusedArgs& a, const PairWalk& first, int kt0, int n, int m0,
-                               int n0, int lane, int8_t* lds, const int2* table) {
+                               int n0, int lane, int8_t* lds, const RgbTap* table) {
     at = first;
     kt = kt0;
     ktiles = a.wrow / 64;
@@ -465,16 +474,15 @@ __global__ __launch_bounds__(kThreads) void k_wide_split(WideFusedArgs a) {
   using Load = typename std::conditional<RGB, WideRgb, WideRing>::type;
   constexpr int STAGES = RGB ? 2 : kSplitD + 1;
   __shared__ __attribute__((aligned(16))) int8_t lds[4 * STAGES * kSplitStage<1>];
-  __shared__ int2 tab[RGB ? 192 : 1];
+  __shared__ RgbTap tab[RGB ? 128 : 1];  // at most 128 taps
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
   const int ktiles = (a.wrow + 63) / 64;
   if constexpr (RGB) {
-    // tap -> (filter row, column), byte offset; past the taps: never inside
     for (int i = tid; i < ktiles * 16; i += kThreads) {
       const int r = i / a.S, s = i - r * a.S;
-      tab[i] = i < a.R * a.S ? make_int2((r << 16) | s, (r * a.W + s) * 4) : make_int2(0x7FFFFFFF, 0);
+      tab[i] = i < a.R * a.S ? RgbTap{r, s, ((int64_t)r * a.W + s) * 4} : RgbTap{INT_MIN / 2, INT_MIN / 2, 0};
     }
     __syncthreads();
   }

@@ -1,7 +1,7 @@
 """Tensors beyond 32-bit indices, against the same calls on cut-outs."""
 import pytest
 
-from gpu_util import DEV, note
+from gpu_util import DEV, fmt_dev, note
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +56,46 @@ def test_first_layer_over_2_32_pixels(fx, h):
     fx.qconv(h, fx.conv_desc(1, R, W, 4, K, R, R, st, 0), cut, fx.U8OFF, w, colsum, None, want)
     torch.cuda.synchronize()
     assert torch.equal(acc[-1:], want)
+
+
+@pytest.mark.parametrize("H,W,pad,st", [(5, 2 ** 27 + 4099, 0, 4096),  # a tap's offset beyond 2 GiB
+                                        (32773, 65541, 2, 1024)])      # more rows and columns than 16 bits count
+def test_wide_first_layer_large_images(fx, h, H, W, pad, st):
+    """The wide contraction pixel by pixel (5x5 filters over padded RGB): every
+    output's pixels against the same pixels as an image of 5x5 cut-outs."""
+    import torch
+    K, R, wl = 4, 5, 9
+    g = torch.Generator(device=DEV).manual_seed(H)
+    note("wide rgb image", H, W)
+    x = torch.full((H, W, 4), 77, dtype=torch.int32, device=DEV)
+    Ho, Wo = (H + 2 * pad - R) // st + 1, (W + 2 * pad - R) // st + 1
+    # the cut-outs: random codes, 0 where a tap is outside the image
+    cut = torch.randint(-256, 256, (Ho, Wo, R, R, 4), generator=g, device=DEV).int()
+    i = (torch.arange(Ho, device=DEV) * st - pad).view(-1, 1, 1, 1) + torch.arange(R, device=DEV).view(1, 1, -1, 1)
+    j = (torch.arange(Wo, device=DEV) * st - pad).view(1, -1, 1, 1) + torch.arange(R, device=DEV).view(1, 1, 1, -1)
+    ok = ((i >= 0) & (i < H) & (j >= 0) & (j < W)).expand(Ho, Wo, R, R)
+    cut[~ok] = 0
+    for r in range(R):
+        for t in range(R):
+            oh = [o for o in range(Ho) if 0 <= o * st - pad + r < H]
+            ow = [o for o in range(Wo) if 0 <= o * st - pad + t < W]
+            r0, t0 = oh[0] * st - pad + r, ow[0] * st - pad + t
+            x[r0::st, t0::st][:len(oh), :len(ow)].copy_(cut[oh[0]:oh[-1] + 1, ow[0]:ow[-1] + 1, r, t])
+    cuts = cut.permute(0, 2, 1, 3, 4).reshape(1, Ho * R, Wo * R, 4).contiguous()
+    w = rgb_filters(g, K, R, -128, 128, torch.int32)
+    ep = fx.epilogue(K, 5, fmt_dev(wl, 4, 1))
+    out = []
+    for a, hh, ww, s, p in ((x, H, W, st, pad), (cuts, Ho * R, Wo * R, R, 0)):
+        d = fx.conv_desc(1, hh, ww, 4, K, R, R, s, p)
+        v = torch.empty((Ho * Wo, K), dtype=torch.int64, device=DEV)
+        nb = fx.qconv_wide_workspace(d, wl, 1, 8, 1)
+        ws = torch.empty(nb, dtype=torch.int8, device=DEV)
+        fx.qconv_wide(h, d, a, wl, 1, w, 8, 1, ep, v, torch.zeros(1, dtype=torch.int32, device=DEV), ws, nb)
+        torch.cuda.synchronize()
+        out.append(v)
+        del ws
+    assert torch.equal(out[0], out[1])
+    assert fx.sync_status(h) == 0
+    # and the cut-outs against fp64 products
+    c = cut.reshape(Ho * Wo, -1).double()
+    assert torch.equal(out[1], (c @ w[:, :R * R * 4].double().t()).long())
