@@ -382,8 +382,9 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
           }
         }
       }
-    } else if (full) {
-      // Full tile: buffer stores with the row offset in a scalar register.
+    } else if (full && a.K < (1 << 21)) {
+      // Full tile: buffer stores with the row offset in a scalar register (at
+      // most 132 rows of 4-byte values below the descriptor's 2 GiB).
       __amdgpu_buffer_rsrc_t rs;
       int vo[TN];
       if constexpr (EPI == EPI_ACC) {

@@ -99,3 +99,18 @@ def test_wide_first_layer_large_images(fx, h, H, W, pad, st):
     # and the cut-outs against fp64 products
     c = cut.reshape(Ho * Wo, -1).double()
     assert torch.equal(out[1], (c @ w[:, :R * R * 4].double().t()).long())
+
+
+def test_contraction_of_long_rows(fx, h):
+    """128 rows of 2^23 outputs: a tile's rows span 4 GiB of accumulators."""
+    import torch
+    M, K, C = 128, 2 ** 23, 16
+    g = torch.Generator(device=DEV).manual_seed(8)
+    note("contraction of long rows")
+    x = torch.randint(-128, 128, (M, C), generator=g, device=DEV).to(torch.int8)
+    w = torch.randint(-128, 128, (K, C), generator=g, device=DEV).to(torch.int8)
+    acc = torch.full((M, K), 7, dtype=torch.int32, device=DEV)
+    fx.qgemm(h, M, K, C, x, fx.I8, w, None, None, acc)
+    torch.cuda.synchronize()
+    for i in range(0, K, K // 8):  # exact in fp32: below 2^24
+        assert torch.equal(acc[:, i:i + K // 8].float(), x.float() @ w[i:i + K // 8].float().t())
