@@ -341,7 +341,8 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
   // The straight-line form: the first candidate does not saturate, and the
   // codes fit the dot product (signed, or no negative values).
   const int var = win ? win_variant(u, ws, a.mm) : 0;  // 2 NN + C0
-  const bool fast = win && (var == 2 || (var == 0 && u.sign));
+  // (its stores' offsets within 64 rows of output stay below the descriptor's range)
+  const bool fast = win && (var == 2 || (var == 0 && u.sign)) && a.K < (1 << 25);
   // Wave priorities: the two blocks of a CU run the same phases, and where both
   // wait for one unit at once the other idles.  With the contraction ahead
   // (deep: the matrix cores are what a tile waits for) or the epilogue ahead

@@ -114,3 +114,34 @@ def test_contraction_of_long_rows(fx, h):
     torch.cuda.synchronize()
     for i in range(0, K, K // 8):  # exact in fp32: below 2^24
         assert torch.equal(acc[:, i:i + K // 8].float(), x.float() @ w[i:i + K // 8].float().t())
+
+
+def test_predicted_cblock_of_long_rows(fx, h):
+    """128 rows of 2^25 + 4 outputs: a tile's rows span 4 GiB of codes."""
+    import torch
+    M, K, C, wl = 128, 2 ** 25 + 4, 16, 8
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randint(-128, 128, (M, 1, 1, C), generator=g, device=DEV).to(torch.int8)
+    w = torch.randint(-128, 128, (K, C), generator=g, device=DEV, dtype=torch.int8)
+    ep = fx.epilogue(K, 9, fmt_dev(8, 5, 1))
+    d = fx.conv_desc(M, 1, 1, C, K, 1, 1, 1, 0)
+    mm = torch.full((2,), float("nan"), dtype=torch.float64, device=DEV)
+    y = torch.full((M, K), 85, dtype=torch.int8, device=DEV)
+    miss = torch.zeros(1, dtype=torch.int32, device=DEV)
+    note("predicted C-Block of long rows")
+    args = (wl, fx.SIGN_AUTO, -8, 15)
+    fx.cblock_predicted(h, d, x, fx.I8, w, None, ep, *args, fmt_dev(wl, 4, 1), y, fx.C8, mm, miss)
+    hits = []
+    for fl in (4, 5):  # the window's candidates: one of them is the format
+        miss.zero_()
+        y.fill_(85)
+        fx.cblock_predicted(h, d, x, fx.I8, w, None, ep, *args, fmt_dev(wl, fl, 1), y, fx.C8, mm, miss)
+        torch.cuda.synchronize()
+        if int(miss) == 0:
+            hits.append(fl)
+            for i in range(0, K, 2 ** 22):
+                v = x.view(M, C).float() @ w[i:i + 2 ** 22].float().t()
+                want = (v * 2.0 ** (fl - 14)).round_().clamp_(-128, 127).to(torch.int8)
+                assert torch.equal(y[:, i:i + 2 ** 22], want), i
+    assert len(hits) == 1
+    assert fx.sync_status(h) == 0
