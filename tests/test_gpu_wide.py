@@ -73,23 +73,25 @@ CASES = [
 ]
 
 
-def run_case(fx, h, orc, case, seed):
+def run_case(fx, h, orc, case, seed, fl_a2=25, epilogue=None):
+    """R: square filters, or (rows, columns).  epilogue: in place of the oracle's."""
     import torch
     N, Cin, H, W, K, R, stride, pad, (wx, sx), (ww, sw), relu, with_bias, with_scale = case
+    R, S = R if isinstance(R, tuple) else (R, R)
     xc = draw(seed, "wx", (N, Cin, H, W), wx, sx)
-    wc = draw(seed, "ww", (K, Cin, R, R), ww, sw)
+    wc = draw(seed, "ww", (K, Cin, R, S), ww, sw)
     x_nhwc = np.transpose(xc, (0, 2, 3, 1))
     w_krsc = np.transpose(wc, (0, 2, 3, 1)).reshape(K, -1)
     cin = Cin
     if Cin == 3:  # padded RGB: a zero fourth channel, filter rows padded to 64
         x_nhwc = np.concatenate([x_nhwc, np.zeros(x_nhwc.shape[:3] + (1,), np.int64)], axis=3)
-        w4 = np.concatenate([np.transpose(wc, (0, 2, 3, 1)), np.zeros((K, R, R, 1), np.int64)], axis=3)
+        w4 = np.concatenate([np.transpose(wc, (0, 2, 3, 1)), np.zeros((K, R, S, 1), np.int64)], axis=3)
         w_krsc = w4.reshape(K, -1)
         kp = (w_krsc.shape[1] + 63) // 64 * 64
         w_krsc = np.concatenate([w_krsc, np.zeros((K, kp - w_krsc.shape[1]), np.int64)], axis=1)
         cin = 4
     g = synth.rng_for(seed, "wepi")
-    fl_x, fl_w, fl_b, fl_a1, fl_a2 = 9, 13, 20, 14, 25
+    fl_x, fl_w, fl_b, fl_a1 = 9, 13, 20, 14
     bias = g.integers(-2 ** 30, 2 ** 30, K).astype(np.int32) if with_bias else None
     a1 = g.integers(-2 ** 15, 2 ** 15, K).astype(np.int32) if with_scale else None
     a2 = g.integers(-2 ** 31, 2 ** 31 - 1, K).astype(np.int32) if with_scale else None
@@ -97,18 +99,18 @@ def run_case(fx, h, orc, case, seed):
     keep = [dev(a) if a is not None else None for a in (bias, a1, a2)]
     ep = fx.epilogue(K, fl_w, fin, bias=keep[0], fl_bias=fl_b, relu=relu, scale=keep[1],
                      fl_scale=fl_a1, shift=keep[2], fl_shift=fl_a2)
-    desc = fx.conv_desc(N, H, W, cin, K, R, R, stride, pad)
+    desc = fx.conv_desc(N, H, W, cin, K, R, S, stride, pad)
     nb = fx.qconv_wide_workspace(desc, wx, sx, ww, sw)
     ws = empty((nb,), torch.uint8)
     Ho = (H + 2 * pad - R) // stride + 1
-    Wo = (W + 2 * pad - R) // stride + 1
+    Wo = (W + 2 * pad - S) // stride + 1
     v = empty((N * Ho * Wo * K,), torch.int64)
     sc = empty((1,), torch.int32)
     note("qconv_wide", case, seed)
     fx.qconv_wide(h, desc, dev(x_nhwc.astype(np.int32)), wx, sx, dev(w_krsc.astype(np.int32)), ww, sw,
                   ep, v, sc, ws, nb)
     acc = orc.conv2d(xc, wc, stride, pad)
-    want, s_out = orc.epilogue(acc, fl_x + fl_w, bias, fl_b, a1, fl_a1, a2, fl_a2, relu)
+    want, s_out = (epilogue or orc.epilogue)(acc, fl_x + fl_w, bias, fl_b, a1, fl_a1, a2, fl_a2, relu)
     want_nhwk = np.transpose(want, (0, 2, 3, 1)).reshape(-1)
     return v, sc, want_nhwk, s_out, keep
 
