@@ -575,21 +575,25 @@ __global__ __launch_bounds__(kThreads) void k_wide_split(WideFusedArgs a) {
 }
 
 // Grids that fill the chip: tiles of 128 x 64 shared by the block's waves (32
-// rows each), slabs through the LDS ring or, padded RGB with filter rows of
+// rows each; 64 x 64, 32 x 32 each, for 128-bit sums: twice the columns held 128
+// registers of sums and spilled as many), slabs through the LDS ring or, padded RGB with filter rows of
 // whole 16-byte chunks, staged through registers four pixels at a time.  Two
 // blocks per CU hide each other's waits (64 x 64 split tiles hold 128 registers
 // of int64 sums per thread, one block: 64 x 224 x 224 padded RGB, the whole
 // C-Block, 1398 us; pixel by pixel with the addresses from the slab's number
 // 976; this 737).
-template <bool RGB>
+template <bool WIDE, bool RGB>
 __global__ __launch_bounds__(kThreads, 2) void k_wide_tile(WideFusedArgs a) {
-  constexpr int BM = 128, BN = 64, SA = BM * 64, ST = (BM + BN) * 64;
+  using Acc = typename std::conditional<WIDE, __int128, int64_t>::type;
+  constexpr int BM = WIDE ? 64 : 128, BN = 64, TN = WIDE ? 1 : 2;
+  constexpr int SA = BM * 64, ST = (BM + BN) * 64;
   using Load = typename std::conditional<RGB, StagedLoad<BM, BN, LD_RGB8>, RingLoad<BM, BN, 4, true>>::type;
   constexpr int D = kSplitD, STAGES = RGB ? 2 : D + 1;
   __shared__ __attribute__((aligned(16))) int8_t stage[STAGES * ST];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const int row0 = (WIDE ? wave >> 1 : wave) * 32, col0 = WIDE ? (wave & 1) * 32 : 0;  // of the wave
   const int ktiles = (a.wrow + 63) / 64;
   const int total = a.np_x * a.np_w * ktiles;
   const ConvArgs ca = conv_args(a);
@@ -616,23 +620,25 @@ __global__ __launch_bounds__(kThreads, 2) void k_wide_tile(WideFusedArgs a) {
       ld.padp = (int64_t)(uintptr_t)&kPadVec[in.off(a) ? 1 : 0];
     }
   };
-  v16i acc[1][2];
-  int64_t W[2][16];
-  int corr[2] = {0, 0};
+  v16i acc[1][TN];
+  Acc W[TN][16];
+  int corr[TN];
 #pragma unroll
-  for (int ni = 0; ni < 2; ++ni)
+  for (int ni = 0; ni < TN; ++ni) {
+    corr[ni] = 0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       acc[0][ni][e] = 0;
       W[ni][e] = 0;
     }
+  }
   int kt = 0;
   // before and after a slab's MFMAs
   auto begin_slab = [&]() __attribute__((always_inline)) {
     if (kt == 0 && at.off(a)) {
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        const int col = n0 + ni * 32 + (lane & 31);
+      for (int ni = 0; ni < TN; ++ni) {
+        const int col = n0 + col0 + ni * 32 + (lane & 31);
         corr[ni] += 128 * a.cs[(int64_t)at.q() * a.K + (col < a.K ? col : a.K - 1)];
       }
     }
@@ -644,10 +650,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_wide_tile(WideFusedArgs a) {
     at.next(a);
     if (at.g == g) return;
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
+    for (int ni = 0; ni < TN; ++ni) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        W[ni][e] += ((int64_t)acc[0][ni][e] + corr[ni]) * ((int64_t)1 << (8 * g));
+        W[ni][e] += ((Acc)acc[0][ni][e] + corr[ni]) * ((Acc)1 << (8 * g));
         acc[0][ni][e] = 0;
       }
       corr[ni] = 0;
@@ -668,13 +674,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_wide_tile(WideFusedArgs a) {
       int8_t *cur = stage + (s & 1) * ST, *next = stage + ((s & 1) ^ 1) * ST;
       begin_slab();
       if (s + 1 < total) load();
-      slab_mfma<1, 2>(cur, cur + SA, wave * 32, 0, lane, acc);
+      slab_mfma<1, TN>(cur, cur + SA, row0, col0, lane, acc);
       if (s + 1 < total) ld.lstore(next, next + SA, tid, padw);
       __syncthreads();
       end_slab();
     }
   } else {
     constexpr int OPS = Load::kOps;
+    static_assert(OPS <= 2 * TN, "every load comes before an MFMA of the slab");
     ld.cols(ca, 0, n0, wave, lane);
     ld.rows(ca, m0, wave, lane);
     ld.padp = (int64_t)(uintptr_t)&kPadVec[in.off(a) ? 1 : 0];
@@ -696,7 +703,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_wide_tile(WideFusedArgs a) {
       ring_barrier();
       int8_t* st = cur == stage ? stage + D * ST : cur - ST;
       const bool more = s + D < total;
-      slab_mfma<1, 2>(cur, cur + SA, wave * 32, 0, lane, acc, [&](int i) __attribute__((always_inline)) {
+      slab_mfma<1, TN>(cur, cur + SA, row0, col0, lane, acc, [&](int i) __attribute__((always_inline)) {
         if (more && i < OPS) ld.load(ca, i, st, st + SA, wave);
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -709,11 +716,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_wide_tile(WideFusedArgs a) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *a.d_scale = u.s_out;
   bool bad = false;
 #pragma unroll
-  for (int ni = 0; ni < 2; ++ni) {
-    const int col = n0 + ni * 32 + (lane & 31);
+  for (int ni = 0; ni < TN; ++ni) {
+    const int col = n0 + col0 + ni * 32 + (lane & 31);
     const EpiRaw r = epi_channel_load(a.ep, col < a.K ? col : a.K - 1);
     wide_store(W[ni], r, u, a.ep, bad, [&](int e, int64_t x) __attribute__((always_inline)) -> bool {
-      const int row = m0 + wave * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+      const int row = m0 + row0 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
       const bool in = row < a.M && col < a.K;
       if (in) a.v[(int64_t)row * a.K + col] = x;
       return in;
@@ -770,10 +777,18 @@ hipError_t launch_acc_overflow(const Ctx& c, const int32_t* acc, int64_t n, int 
 // Fused contraction's variant: 32 x 32 split tiles up to eight per CU (fewer
 // 128 x 64 tiles than CUs: 4536 x 128 x 144, 568 split tiles, 44 us against 57 in
 // 72 tiles; 10 x 207 x 207 padded RGB, 6500 split tiles, 182 against 115 in 813),
-// for 128-bit sums (256 registers of 128 x 64 tiles), and for padded RGB whose
-// filter rows do not fit the packed rows as whole chunks; else 128 x 64 tiles.
+// and for padded RGB whose filter rows do not fit the packed rows as whole
+// chunks; else 128 x 64 tiles.  128-bit sums: split tiles, but 64 x 64 ones for
+// grids above 24 split tiles per CU with at most 16 slabs (the split tiles'
+// exchange of sums, 16 barriers, outweighs the contraction) and full column
+// tiles.  24 / 32 by 16 / 24 bits (9 / 16 slabs), us, split -> 64 x 64: 802816 x 64
+// x 16 711 -> 555, 837 -> 734; 200704 x 128 x 48 360 -> 289, 428 -> 384; but 50176
+// x 64 x 16 (3136 split tiles) 57 -> 54, 67 -> 71, 802816 x 16 x 64 408 -> 589, and
+// 12544 x 512 x 256 (36 slabs) 126 -> 132.
 static bool wide_split_tiles(const Ctx& c, const WideFusedArgs& a, bool wide) {
-  return wide || (int64_t)((a.M + 31) / 32) * ((a.K + 31) / 32) <= 8 * c.cus;
+  const int64_t ct = (a.K + 31) / 32, tiles = (int64_t)((a.M + 31) / 32) * ct;
+  if (!wide) return tiles <= 8 * c.cus;
+  return tiles <= 24 * c.cus || a.np_x * a.np_w * ((a.wrow + 63) / 64) > 16 || ct % 2 != 0;
 }
 
 int wide_chunks(const Ctx& c, const WideFusedArgs& a, bool wide) {
@@ -801,9 +816,12 @@ hipError_t launch_wide_fused(const Ctx& c, const WideFusedArgs& args, bool wide)
     else if (rgb) k_wide_split<false, true><<<grid, kThreads, 0, c.stream>>>(a);
     else k_wide_split<false, false><<<grid, kThreads, 0, c.stream>>>(a);
   } else {
-    const dim3 grid((unsigned)((a.M + 127) / 128), (unsigned)((a.K + 63) / 64));
-    if (rgb) k_wide_tile<true><<<grid, kThreads, 0, c.stream>>>(a);
-    else k_wide_tile<false><<<grid, kThreads, 0, c.stream>>>(a);
+    const int bm = wide ? 64 : 128;
+    const dim3 grid((unsigned)((a.M + bm - 1) / bm), (unsigned)((a.K + 63) / 64));
+    if (wide && rgb) k_wide_tile<true, true><<<grid, kThreads, 0, c.stream>>>(a);
+    else if (wide) k_wide_tile<true, false><<<grid, kThreads, 0, c.stream>>>(a);
+    else if (rgb) k_wide_tile<false, true><<<grid, kThreads, 0, c.stream>>>(a);
+    else k_wide_tile<false, false><<<grid, kThreads, 0, c.stream>>>(a);
   }
   return hipGetLastError();
 }

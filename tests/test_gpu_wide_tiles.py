@@ -49,20 +49,39 @@ LARGE = [
     (1, 3, 183, 181, 36, 5, 1, 2, (16, 0), (10, 1), False, True, False),    # rows that do not fit: 32 x 32 tiles
 ]
 
+# 128-bit sums of few slabs in more 32 x 32 tiles than 24 per CU: 64 x 64 tiles
+LARGE128 = [
+    (1, 16, 317, 311, 36, 1, 1, 0, (24, 0), (16, 1), True, True, False),   # a quarter of a slab per pair
+    (1, 48, 230, 231, 100, 1, 1, 0, (24, 1), (16, 1), False, False, True),  # two column tiles
+    (3, 16, 130, 263, 52, 2, 1, 1, (32, 1), (24, 1), False, True, False),  # four taps, sixteen pairs
+    (1, 3, 317, 313, 36, 3, 1, 1, (24, 1), (16, 1), True, True, False),    # padded RGB
+    (2, 3, 226, 227, 36, (1, 9), 1, 0, (32, 1), (15, 0), False, True, False),  # three chunks per filter row
+    (1, 16, 260, 259, 68, 1, 1, 0, (24, 0), (16, 1), True, True, False),   # an odd number of column tiles: 32 x 32
+]
 
-def many_tiles(case):
+
+def many_tiles(case, per_cu=8):
     import torch
     N, _, H, W, K, R, stride, pad = case[:8]
     R, S = R if isinstance(R, tuple) else (R, R)
     M = N * ((H + 2 * pad - R) // stride + 1) * ((W + 2 * pad - S) // stride + 1)
     assert M % 128 and K % 64
-    return -(-M // 32) * -(-K // 32) > 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    return -(-M // 32) * -(-K // 32) > per_cu * torch.cuda.get_device_properties(0).multi_processor_count
 
 
 @pytest.mark.parametrize("case", LARGE, ids=[str(i) for i in range(len(LARGE))])
 def test_wide_large_tiles(fx, h, orc, case):  # noqa: F811
     assert many_tiles(case)
     v, sc, want, s_out, _ = run_case(fx, h, orc, case, seed=240 + LARGE.index(case))
+    assert int(host(sc)[0]) == s_out
+    assert np.array_equal(host(v), want)
+    assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("case", LARGE128, ids=[str(i) for i in range(len(LARGE128))])
+def test_wide_large_tiles_128_bits(fx, h, orc, case):  # noqa: F811
+    assert many_tiles(case, 24)
+    v, sc, want, s_out, _ = run_case(fx, h, orc, case, seed=250 + LARGE128.index(case))
     assert int(host(sc)[0]) == s_out
     assert np.array_equal(host(v), want)
     assert fx.sync_status(h) == 0
