@@ -171,35 +171,36 @@ __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, 
                                      int fl_lo, int fl_hi, int mode, int64_t per_thread) {
   WinSetup w;
   w.u = fls_uniform<KIND>(s, mm, wl, sign_req, fl_lo, fl_hi);
-  const double wmax = w.u.absmax * w.u.wscale;
   const double qabs = fmax(w.u.qmax, -w.u.qmin);
-  w.verdict = 0;
-  if (!w.u.ok) w.verdict = 3;
-  else if (mode == MODE_REPORT || wl > 16 || wl == 1 || wmax >= kTwo52) w.verdict = 2;
-  else if (w.u.beta_nosat >= fl_hi) w.verdict = 1;
-  else if (KIND != FXPQ_SRC_F32 && wmax * qabs * (double)per_thread >= kTwo53 &&
-           (!SPLIT || ldexp(w.u.absmax, imax(fl_hi - w.u.sv, 0)) >= 0x1p62))
-    w.verdict = 2;
   w.b0 = imax(fl_lo, w.u.beta_nosat);
   w.b1 = (w.b0 + kWindow - 1 < fl_hi) ? w.b0 + kWindow - 1 : fl_hi;
   w.nc = w.b1 - w.b0 + 1;
   w.bce = (w.b1 < fl_hi) ? w.b1 + 1 : w.b1;
   w.split = SPLIT;
+  bool range = false;
   if constexpr (KIND == FXPQ_SRC_F32) {
     // fp32 values in units of 2^-(b1 + 24): an integer wherever a window code is
     // not 0 (|v| >= 2^-(b1 + 1), 24-bit mantissa).  Small word lengths need no
     // split then: where the first candidate does not saturate, |W| <= (qabs + 1)
-    // 2^(b1 - b0 + 24).  The rule looks at the window alone, not at the values'
-    // magnitude: a predicted call forms its sums with the previous min / max and
-    // decides with this call's, and both have to choose the same units wherever
+    // 2^(b1 - b0 + 24).  Units and split depend on the window alone, not on the
+    // values' magnitude: a predicted call forms its sums with the previous min /
+    // max and decides with this call's, and both have to choose the same wherever
     // they agree on the window.
-    if (w.verdict == 0 && w.b0 == w.u.beta_nosat &&
-        ldexp((qabs + 1.0) * qabs * (double)per_thread, w.b1 - w.b0 + 24) < kTwo53) {
+    range = w.u.ok && ldexp(w.u.absmax, w.u.sigma) >= 0x1p62;  // the exact pass's error
+    w.u.sigma = w.b1 + 24;
+    w.u.wscale = ldexp(1.0, w.u.sigma);
+    if (w.b0 == w.u.beta_nosat &&
+        ldexp((qabs + 1.0) * qabs * (double)per_thread, w.b1 - w.b0 + 24) < kTwo53)
       w.split = 0;
-      w.u.sigma = w.b1 + 24;
-      w.u.wscale = ldexp(1.0, w.u.sigma);
-    }
   }
+  const double wmax = w.u.absmax * w.u.wscale;
+  w.verdict = 0;
+  if (!w.u.ok) w.verdict = 3;
+  else if (mode == MODE_REPORT || wl > 16 || wl == 1 || range || wmax >= kTwo52) w.verdict = 2;
+  else if (w.u.beta_nosat >= fl_hi) w.verdict = 1;
+  else if (KIND != FXPQ_SRC_F32 && wmax * qabs * (double)per_thread >= kTwo53 &&
+           (!SPLIT || ldexp(w.u.absmax, imax(fl_hi - w.u.sv, 0)) >= 0x1p62))
+    w.verdict = 2;
   return w;
 }
 

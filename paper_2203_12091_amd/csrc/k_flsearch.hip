@@ -73,7 +73,7 @@ __device__ inline void win_loop(const SrcDev& s, int64_t n, const FlsU& u, const
   auto consume = [&](double v, int* cq) {
     double q[kWindow];
     // integer sources are searched at sigma = sv (W = v); fp32 values are
-    // scaled, exactly
+    // scaled, exactly (an integer wherever a code is not 0)
     if constexpr (SPLIT) win_consume<true, NONNEG, CLAMP0, NB>(wc, acc, KIND == FXPQ_SRC_F32 ? v * post : v, q);
     else win_consume_x<NONNEG, CLAMP0, NB>(wx, acc, v * wx.xs, q);
     if constexpr (CODES) {
@@ -927,14 +927,19 @@ __device__ void general_sums(const SrcDev& s, int64_t n, int wl, const FlsU& u, 
   }
 }
 
-// The same sums of int64 values 2^52 <= max |W| < 2^62 (W = v): W in three
-// parts of 26, 26 and 10 bits, and its code from a double that holds W rounded
+// The same sums of values 2^52 <= max |W| < 2^62: W in three parts of 26, 26
+// and 10 bits.  int64 values (W = v): the code from a double that holds W rounded
 // to odd above 2^53 (a code that uses bits below 2^10 of such a W is clamped;
-// above, the odd last bit keeps a tie from appearing or vanishing).  Wide
-// C-Blocks at 24 bits against the 128-bit errors: 244800 values 223 -> 123 us,
-// 4.6 M 1130 -> 222.
-__device__ inline void general_sums_i64(const int64_t* x, int64_t n, int wl, const FlsU& u,
-                                        const GenPlan& g, unsigned long long* part) {
+// above, the odd last bit keeps a tie from appearing or vanishing).  The other
+// sources' W are doubles and the code comes from them; an fp32 W that is not an
+// integer is below 2^23, its codes are 0 (fl <= sigma - 24) and its parts count
+// for nothing.  Wide C-Blocks at 24 bits against the 128-bit errors: 244800
+// values 223 -> 123 us, 4.6 M 1130 -> 222.
+template <int KIND, int DT>
+__device__ inline void general_sums_wide(const SrcDev& s, int64_t n, int wl, const FlsU& u,
+                                         const GenPlan& g, unsigned long long* part) {
+  constexpr bool I64 = KIND == FXPQ_SRC_INT && DT == FXPQ_I64;
+  using Val = std::conditional_t<I64, long long, double>;
   __shared__ long long sh[4][kGenGroup][8];
   const int flush_at = gen_flush(wl);
   const int nc = gen_count(g);
@@ -954,10 +959,18 @@ __device__ inline void general_sums_i64(const int64_t* x, int64_t n, int wl, con
         I[k][i] = 0;
       }
     }
-    auto add = [&](long long W) {
-      const long long odd = ((W >> 10) | ((W & 1023) != 0 ? 1 : 0));
-      const bool small = W < (1ll << 53) && W > -(1ll << 53);
-      const double Wd = small ? (double)W : (double)odd * 1024.0;
+    auto load = [&](int64_t i) -> Val {
+      if constexpr (I64) return static_cast<const int64_t*>(s.x)[i];
+      else return load1<KIND, DT>(s, i) * u.wscale;
+    };
+    auto add = [&](Val v) {
+      const long long W = (long long)v;
+      double Wd = v;
+      if constexpr (I64) {
+        const long long odd = ((W >> 10) | ((W & 1023) != 0 ? 1 : 0));
+        const bool small = W < (1ll << 53) && W > -(1ll << 53);
+        Wd = small ? (double)W : (double)odd * 1024.0;
+      }
       const double p0 = (double)(int)(W & M26), p1 = (double)(int)((W >> 26) & M26),
                    p2 = (double)(int)(W >> 52);
 #pragma unroll
@@ -971,9 +984,9 @@ __device__ inline void general_sums_i64(const int64_t* x, int64_t n, int wl, con
     };
     int cnt = 0;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += V * stride) {
-      long long w[V];
+      Val w[V];
 #pragma unroll
-      for (int v = 0; v < V; ++v) w[v] = i + v * stride < n ? x[i + v * stride] : 0;  // 0 adds nothing
+      for (int v = 0; v < V; ++v) w[v] = i + v * stride < n ? load(i + v * stride) : (Val)0;  // 0 adds nothing
 #pragma unroll
       for (int v = 0; v < V; ++v) add(w[v]);
       cnt += V;
@@ -1108,12 +1121,16 @@ __device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, 
   }
   const long long qmax = (1ll << (wl - sign)) - 1;
   const long long qmin = sign ? -(1ll << (wl - 1)) : 0;
-  // Word lengths 2..25 with integers |W| < 2^52 (fp32: W = v 2^(fl_hi + 24)):
-  // the candidates' exact sums in fp64, four per read of the values; int64
-  // values over their whole range.  A block's sum q^2 has to fit 63 bits.
+  // Word lengths 2..25: the candidates' exact sums in fp64 of W = v 2^(fl_hi + 24)
+  // (fp32) or v, four per read of the values.  A block's sum q^2 has to fit 63
+  // bits.  Every block reduces every candidate's sums (3 us per four of the
+  // three-part ones): where the 128-bit errors' items, one per candidate and 65536
+  // values, spread over the blocks, few values go there (24 candidates of 12000
+  // fp32 values 57 against 72 us, of 100000 115 against 80).
   const int sigf = (KIND == FXPQ_SRC_F32) ? sigma : sv;
+  const bool parts3 = absmax * ldexp(1.0, sigf - sv) >= kTwo52;
   if (wl >= 2 && gen_flush(wl) >= Pack<KIND, DT>::EP && !d_sse &&
-      (absmax * ldexp(1.0, sigf - sv) < kTwo52 || (KIND == FXPQ_SRC_INT && DT == FXPQ_I64)) &&
+      (!parts3 || (KIND == FXPQ_SRC_INT && DT == FXPQ_I64) || gridDim.x == 1 || n >= 32768) &&
       ldexp((double)(n / gridDim.x + kThreads * Pack<KIND, DT>::EP * kWinSets), 2 * wl) < 0x1p62) {
     const FlsU u = fls_uniform<KIND>(s, mm, wl, sign, fl_lo, fl_hi);
     // candidates below beta_nosat never win (see the top of this file); int64
@@ -1121,12 +1138,8 @@ __device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, 
     const int nosat = u.beta_nosat - (KIND == FXPQ_SRC_INT && DT == FXPQ_I64 && absmax >= kTwo53 ? 1 : 0);
     const int lo = extra == INT_MIN ? imax(glo, nosat < ghi ? nosat : ghi) : glo;
     const GenPlan gf{1, 0, sign, lo, ghi, extra};
-    bool wide = false;
-    if constexpr (KIND == FXPQ_SRC_INT && DT == FXPQ_I64) {
-      wide = absmax >= kTwo52;
-      if (wide) general_sums_i64(static_cast<const int64_t*>(s.x), n, wl, u, gf, part);
-    }
-    if (!wide) general_sums<KIND, DT>(s, n, wl, u, gf, part);
+    if (parts3) general_sums_wide<KIND, DT>(s, n, wl, u, gf, part);
+    else general_sums<KIND, DT>(s, n, wl, u, gf, part);
     __threadfence();
     __syncthreads();
     if (threadIdx.x == 0) last = atomicAdd(done, 1u) == gridDim.x - 1;
@@ -1260,10 +1273,10 @@ __global__ __launch_bounds__(kThreads) void k_fls_general(
 
 // Search of a small tensor in one launch of one block: the min / max (unless
 // given), the window's sums in LDS slots, the decision, and the exact pass when
-// it leaves candidates.  Bound by the latency of its steps; the four launches
-// it replaces (min / max and its finish, window, decision) are mostly launch.
-// int64 values leave the exact pass to its own launch: beyond 2^52 it works in
-// 128 bits, candidate by candidate, far too long for one block.
+// it leaves candidates (as sums: the 128-bit errors, candidate by candidate, would
+// be far too long for one block).  Bound by the latency of its steps; the four
+// launches it replaces (min / max and its finish, window, decision) are mostly
+// launch.  int64 values leave the exact pass to its own launch.
 constexpr bool small_general(int kind, int dt) { return !(kind == FXPQ_SRC_INT && dt == FXPQ_I64); }
 
 template <int KIND, int DT>
@@ -1495,7 +1508,7 @@ static hipError_t fl_search_passes(const Ctx& c, const SrcDev& s, int64_t n, int
 // 256 9.2 / 15.1, 4096 10.6 / 16.3, 8192 12.8 / 16.8, 16384 17.2 / 16.7; half of
 // that when it is given: 256 7.6 / 8.8, 4096 8.6 / 9.4, 8192 10.1 / 9.6), word lengths of the window; C-Block values with the
 // thread's channels fixed over one block's stride; fp32 only for fl_hi that
-// keep ordinary values (below 4096) out of the 128-bit pass.
+// keep ordinary values (below 4096) in the exact pass's two-part sums.
 constexpr int64_t kSmallSearch = 8192;
 static bool small_search(const SrcDev& s, int64_t n, int wl, int fl_hi, bool have_mm) {
   return n <= (have_mm ? kSmallSearch / 2 : kSmallSearch) && wl >= 2 && wl <= 16 &&

@@ -156,3 +156,76 @@ def test_int64_extreme_rounded_to_the_bound(fx, h, orc, n, wl):
                 ofl, osign, _ = orc.fl_search_i64(v, s, wl, sign, FL_LO, FL_HI)
                 assert fmt_host(out) == (wl, ofl, osign, 0), (sign, k, du)
     assert fx.sync_status(h) == 0
+
+
+def search(fx, h, src, n, wl, lo, hi, sse=None):
+    out = fmt_new()
+    fx.fl_search(h, src, n, wl, fx.SIGN_AUTO, lo, hi, out, sse)
+    return fmt_host(out)
+
+
+@pytest.mark.parametrize("n", [1, 5, 256, 4096, 8192, 8193, 300_001])
+@pytest.mark.parametrize("wl", [2, 4, 8, 13, 16, 24])
+def test_f32_search_large_values(fx, h, orc, n, wl):
+    """fp32 values of 2^12 and more units of the largest fl (W = v 2^(fl_hi + 24)
+    from 2^52 on): three-part sums of the exact pass, in one block and in many,
+    with small and fractional W beside them; saturated at the lowest fl, ties
+    of the candidates' codes."""
+    import torch
+    g = synth.rng_for(n + wl, "f32-large")
+    for lo, hi, e in ((-8, 15, 14), (-8, 15, 22), (-20, 16, 20), (-64, 3, 30)):
+        v = g.standard_normal(n) * 2.0 ** (e - 3)
+        pick = g.integers(0, 4, n)
+        v = np.where(pick == 0, v * 2.0 ** -g.integers(0, 60, n), v)
+        v = np.where(pick == 1, (2 * g.integers(-2 ** 7, 2 ** 7, n) + 1) * 2.0 ** g.integers(-hi, 9, n), v)
+        v[n // 2] = 2.0 ** e * 1.37
+        v = v.astype(np.float32)
+        assert 2 ** 52 <= np.abs(v).max() * 2.0 ** (hi + 24) < 2 ** 62
+        note("f32 large", n, wl, lo, hi, e)
+        vd = dev(v)
+        ofl, osign, _ = orc.fl_search_f32(v, wl, fx.SIGN_AUTO, lo, hi)
+        assert search(fx, h, fx.src_f32(vd), n, wl, lo, hi) == (wl, ofl, osign, 0)
+        mm = torch.tensor([float(v.min()), float(v.max())], dtype=torch.float64, device=DEV)
+        assert search(fx, h, fx.src_f32(vd, mm), n, wl, lo, hi) == (wl, ofl, osign, 0)
+        if wl > 8:
+            continue
+        codes, y, alt = (torch.empty(n + 16, dtype=torch.int8, device=DEV) for _ in range(3))
+        fx.quantize(h, vd, n, fmt_dev(wl, ofl, osign), codes, fx.C8)
+        out = fmt_new()
+        fx.qlayer(h, fx.src_f32(vd), n, wl, fx.SIGN_AUTO, lo, hi, out, y, fx.C8, alt)
+        assert fmt_host(out) == (wl, ofl, osign, 0) and torch.equal(y[:n], codes[:n])
+        miss = torch.zeros(1, dtype=torch.int32, device=DEV)
+        y.fill_(99)
+        fx.qlayer_predicted(h, fx.src_f32(vd), n, wl, fx.SIGN_AUTO, lo, hi, out, y, fx.C8, mm, miss)
+        if int(miss) == 0:
+            assert fmt_host(out) == (wl, ofl, osign, 0) and torch.equal(y[:n], codes[:n])
+        else:
+            assert int(miss) == 2  # the window alone does not decide
+    assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("n", [64, 4096, 20_000])
+@pytest.mark.parametrize("wl", [4, 8, 16, 20])
+def test_integer_search_of_53_bits(fx, h, orc, n, wl):
+    """C-Block values and residual sums of 2^52 <= |W| < 2^53."""
+    g = synth.rng_for(n + wl, "53")
+    ch = 32
+    acc = np.clip(g.standard_normal(n) * 2.0 ** 27, -2 ** 30 + 1, 2 ** 30 - 1).astype(np.int32).reshape(-1, ch)
+    acc[1, 3] = 2 ** 30 - 5
+    a1 = g.integers(2 ** 22, 2 ** 23, ch).astype(np.int32)
+    ep = fx.epilogue(ch, 24, fmt_dev(8, 20, 1), scale=dev(a1), fl_scale=10)
+    v, s = orc.epilogue(acc.astype(np.int64), 44, a1=a1, fl_a1=10)
+    assert 2 ** 52 <= np.abs(v).max() < 2 ** 53
+    note("53 bits", n, wl)
+    for lo, hi in ((FL_LO, FL_HI), (-30, 40)):
+        ofl, osign, _ = orc.fl_search_i64(np.ravel(v), s, wl, fx.SIGN_AUTO, lo, hi)
+        assert search(fx, h, fx.src_acc(dev(acc), ep), n, wl, lo, hi) == (wl, ofl, osign, 0)
+    a, b = g.integers(0, 256, n), g.integers(-128, 128, n)
+    a[n // 2] = 255
+    src = fx.src_add(dev((a - 128).astype(np.int8)), fx.C8, fmt_dev(8, 0, 0), dev(b.astype(np.int8)), fx.C8,
+                     fmt_dev(8, 45, 1), False)
+    w = (a.astype(np.int64) << 45) + b
+    for lo, hi in ((FL_LO, FL_HI), (-20, 44)):
+        ofl, osign, _ = orc.fl_search_i64(w, 45, wl, fx.SIGN_AUTO, lo, hi)
+        assert search(fx, h, src, n, wl, lo, hi) == (wl, ofl, osign, 0)
+    assert fx.sync_status(h) == 0
