@@ -1423,11 +1423,14 @@ static hipError_t general_pass(const Ctx& c, const SrcDev& s, int64_t n, int wl,
   int nchunks = (int)((n + 65535) / 65536);
   if (nchunks > kGenChunks) nchunks = kGenChunks;
   if (nchunks < 1) nchunks = 1;
-  // about a block per CU; for C-Block values the grid stride is a multiple of
-  // the channels where at most kGenChunks blocks allow it
+  // about a block per CU (one where it alone has values and forms sums, which
+  // every block reduces for every candidate: 256 int32 values at 17 bits 34 -> 18
+  // us, with an outlier 49 -> 33); for C-Block values the grid stride is a multiple of the channels where at
+  // most kGenChunks blocks allow it
+  const int per = kThreads * 4;  // values per block and iteration
   int gblocks = 240;
+  if (s.kind != FXPQ_SRC_F32 && !d_sse && wl >= 2 && wl <= 23 + (s.kind != FXPQ_SRC_ADD) && n <= per) gblocks = 1;
   if (s.kind == FXPQ_SRC_ACC) {
-    const int per = kThreads * 4;  // values per block and iteration
     int a = s.channels, b = per;
     while (b) {
       const int t = a % b;
@@ -1435,7 +1438,7 @@ static hipError_t general_pass(const Ctx& c, const SrcDev& s, int64_t n, int wl,
       b = t;
     }
     const int g = s.channels / a;
-    if (g <= kGenChunks) gblocks = g * imax(1, 240 / g);
+    if (g <= kGenChunks) gblocks = g * imax(1, gblocks / g);
   }
   FXPQ_DISPATCH_SRC(s.kind, s.dtype,
                     (k_fls_general<K_, D_><<<gblocks, kThreads, 0, c.stream>>>(

@@ -229,3 +229,37 @@ def test_integer_search_of_53_bits(fx, h, orc, n, wl):
         ofl, osign, _ = orc.fl_search_i64(w, 45, wl, fx.SIGN_AUTO, lo, hi)
         assert search(fx, h, src, n, wl, lo, hi) == (wl, ofl, osign, 0)
     assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("n", [1, 16, 256, 1023, 1024, 1025])
+@pytest.mark.parametrize("wl", [17, 20, 23, 24, 25])
+def test_exact_pass_of_one_block(fx, h, orc, n, wl):
+    """Word lengths past the window's, up to the values of one block and one more
+    (there the exact pass is one block): every source but fp32, which is there
+    to compare."""
+    import torch
+    g = synth.rng_for(n + wl, "one-block")
+    v = values(n * wl, n, 24, True)
+    sd = torch.tensor([9], dtype=torch.int32, device=DEV)
+    note("one block", n, wl)
+    want = (wl, *orc.fl_search_i64(v, 9, wl, fx.SIGN_AUTO, FL_LO, FL_HI)[:2], 0)
+    assert search(fx, h, fx.src_int(dev(v.astype(np.int32)), fx.I32, sd), n, wl, FL_LO, FL_HI) == want
+    assert search(fx, h, fx.src_int(dev(v), fx.I64, sd), n, wl, FL_LO, FL_HI) == want
+    x = v.astype(np.float32)
+    fl, sg, _ = orc.fl_search_f32(x * np.float32(2.0 ** -9), wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+    assert search(fx, h, fx.src_f32(dev(x * np.float32(2.0 ** -9))), n, wl, FL_LO, FL_HI) == (wl, fl, sg, 0)
+    for ch in (1, 12, 1000):
+        rows = max(1, n // ch)
+        acc = g.integers(-2 ** 22, 2 ** 22, (rows, ch)).astype(np.int32)
+        a1 = g.integers(2 ** 14, 2 ** 15, ch).astype(np.int32)
+        ep = fx.epilogue(ch, 9, fmt_dev(8, 5, 1), scale=dev(a1), fl_scale=15)
+        w, s = orc.epilogue(acc.astype(np.int64), 14, a1=a1, fl_a1=15)
+        fl, sg, _ = orc.fl_search_i64(np.ravel(w), s, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+        assert search(fx, h, fx.src_acc(dev(acc), ep), acc.size, wl, FL_LO, FL_HI) == (wl, fl, sg, 0)
+    a, b = g.integers(0, 256, n), g.integers(-128, 128, n)
+    src = fx.src_add(dev((a - 128).astype(np.int8)), fx.C8, fmt_dev(8, 5, 0), dev(b.astype(np.int8)), fx.C8,
+                     fmt_dev(8, 9, 1), True)
+    w = np.maximum((a.astype(np.int64) << 4) + b, 0)
+    fl, sg, _ = orc.fl_search_i64(w, 9, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+    assert search(fx, h, src, n, wl, FL_LO, FL_HI) == (wl, fl, sg, 0)
+    assert fx.sync_status(h) == 0
