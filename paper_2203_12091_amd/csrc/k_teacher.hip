@@ -210,6 +210,38 @@ __global__ __launch_bounds__(256, 4) void k_teacher_conv(const float* __restrict
   }
 }
 
+// The same chains one output per thread, output channels fastest so a wave reads
+// few input pixels and consecutive filters: for outputs whose 32 x 32 tiles would be
+// mostly padding (narrow_teacher).  Bound by the loads of the pixels, which
+// neighbouring threads share.
+__global__ __launch_bounds__(256) void k_teacher_narrow(const float* x, const float* w, float* y,
+                                                        int N, int H, int W, int C, int K, int R,
+                                                        int S, int stride, int pad, int Ho, int Wo) {
+  const int64_t total = (int64_t)N * Ho * Wo * K;
+  for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < total;
+       o += (int64_t)gridDim.x * blockDim.x) {
+    const int k = (int)(o % K);
+    int64_t pix = o / K;
+    const int ow = (int)(pix % Wo);
+    pix /= Wo;
+    const int oh = (int)(pix % Ho);
+    const int n = (int)(pix / Ho);
+    double acc = 0.0;
+    for (int r = 0; r < R; ++r) {
+      const int ih = oh * stride - pad + r;
+      if (ih < 0 || ih >= H) continue;
+      for (int s = 0; s < S; ++s) {
+        const int iw = ow * stride - pad + s;
+        if (iw < 0 || iw >= W) continue;
+        const float* xp = x + (((int64_t)n * H + ih) * W + iw) * C;
+        const float* wp = w + ((int64_t)(r * S + s) * C) * K + k;
+        for (int c = 0; c < C; ++c) acc = fma((double)xp[c], (double)wp[(int64_t)c * K], acc);
+      }
+    }
+    y[o] = (float)acc;
+  }
+}
+
 // Per channel (innermost, `channels` of them): fmaf(t, a1, a2) or t + bias,
 // then ReLU.  In place allowed.
 __global__ __launch_bounds__(256) void k_teacher_affine(const float* t, int64_t n, int channels,
@@ -282,11 +314,32 @@ static int elem_grid(int64_t n) {
   return (int)(b < 65536 ? (b < 1 ? 1 : b) : 65536);
 }
 
+// Outputs that one thread each computes faster than 32 x 32 tiles: few and
+// shallow ones (a tile takes its 32 channels and 32 of depth whatever exists of
+// them), and up to eight channels of a few input channels.  us, per output / in
+// tiles, pixels x channels, depth: 784 x 64, 1 5.1 / 6.4; 12544 x 16, 9 5.2 / 7.2;
+// 802816 x 4, 4 15 / 61, x 16 52 / 63, x 24 75 / 64; 802816 x 1, 9 10 / 77, x 8 57 /
+// 79, x 12 84 / 80; 802816 x 8, 147 (3 input channels) 374 / 439, 100352 x 4 31 / 69,
+// x 12 67 / 69, but 784 x 4 17 / 11; 16 input channels, 100352 x 4, 144 25 / 50, x 8
+// 37 / 51, x 2 66 / 56, x 6 144 / 57; 64, x 4, 576 218 / 185.
+static bool narrow_teacher(int64_t M, int K, int C, int64_t depth) {
+  const int64_t one = K * (depth + 3);  // about a pixel's work
+  if (one <= (C <= 4 ? 128 : 64) || (depth <= 16 && M * one <= 2500000)) return true;
+  if (K > 8) return false;
+  if (C <= 4) return depth <= 32 || M >= 65536;
+  return C <= 16 && M >= 65536 && (K == 1 || K % 4 == 0);
+}
+
 hipError_t launch_teacher_conv(const Ctx& c, const fxpq_conv_desc& d, const float* x,
                                const float* w, float* y) {
   const int Ho = (d.h + 2 * d.pad - d.r) / d.stride + 1;
   const int Wo = (d.w + 2 * d.pad - d.s) / d.stride + 1;
   const int64_t M = (int64_t)d.n * Ho * Wo;
+  if (narrow_teacher(M, d.k, d.c, (int64_t)d.r * d.s * d.c)) {
+    k_teacher_narrow<<<elem_grid(M * d.k), 256, 0, c.stream>>>(x, w, y, d.n, d.h, d.w, d.c, d.k, d.r, d.s,
+                                                               d.stride, d.pad, Ho, Wo);
+    return hipGetLastError();
+  }
   auto blocks = [&](int b) { return ((M + b - 1) / b) * ((d.k + b - 1) / b); };
   auto run = [&](auto kernel, int b) {
     const int64_t tiles = blocks(b);

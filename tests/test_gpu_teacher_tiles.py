@@ -2,7 +2,7 @@
 can go wrong: pixel, channel and depth remainders of both block sizes, channel
 counts and pointers that do not allow 16-byte loads, several filter taps per
 slab, and infinite or NaN values (a padded tap is skipped, not multiplied by
-0)."""
+0); and narrow outputs, one per thread."""
 import numpy as np
 import pytest
 
@@ -40,6 +40,13 @@ CASES = [  # n, c, h, w, k, r, stride, pad
     (5, 2048, 1, 1, 1000, 1, 1, 0),
     (33, 48, 33, 31, 132, 3, 1, 1),  # large blocks (over four per CU), remainders in every direction
     (17, 7, 65, 63, 67, 3, 1, 0),    # large blocks, scalar loads
+    (2, 3, 9, 7, 45, 3, 1, 1),       # small blocks, four and more taps per slab, scalar loads
+    (1, 1, 33, 9, 40, 5, 1, 2),      # a tap per value
+    # narrow: shallow, few input channels, few output channels
+    (3, 1, 28, 29, 31, 1, 1, 0),
+    (1, 3, 300, 251, 6, 5, 1, 2),
+    (5, 16, 131, 120, 4, 1, 1, 0),
+    (2, 12, 7, 9, 3, 1, 2, 1),
 ]
 
 
