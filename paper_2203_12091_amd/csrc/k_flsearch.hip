@@ -820,7 +820,7 @@ constexpr int kGenGroup = 4;
 constexpr int kGenFlush = 512;  // values per thread between flushes (as kWinMaxPerThread)
 // ... so that its sums of q^2 < 2^(2 wl) and of Wh q, Wl q < 2^(26 + wl) stay
 // below 2^53 (0: word lengths the pass does not take).
-__device__ inline int gen_flush(int wl) {
+__host__ __device__ inline int gen_flush(int wl) {
   return wl <= 18 ? kGenFlush : (wl <= 25 ? 1 << (27 - wl) : 0);
 }
 
@@ -1423,14 +1423,17 @@ static hipError_t general_pass(const Ctx& c, const SrcDev& s, int64_t n, int wl,
   int nchunks = (int)((n + 65535) / 65536);
   if (nchunks > kGenChunks) nchunks = kGenChunks;
   if (nchunks < 1) nchunks = 1;
-  // about a block per CU (one where it alone has values and forms sums, which
-  // every block reduces for every candidate: 256 int32 values at 17 bits 34 -> 18
-  // us, with an outlier 49 -> 33); for C-Block values the grid stride is a multiple of the channels where at
-  // most kGenChunks blocks allow it
+  // about a block per CU.  Where the pass forms sums: one block where it alone has
+  // values (every block reduces every candidate's sums: 256 int32 values at 17 bits
+  // 34 -> 18 us, with an outlier 49 -> 33); for C-Block values the grid stride is a
+  // multiple of the channels where at most kGenChunks blocks allow it (the 128-bit
+  // errors take whatever blocks there are: every error of 500000 values in 135
+  // blocks 310 us, in 240 177).
   const int per = kThreads * 4;  // values per block and iteration
+  const bool sums = !d_sse && wl >= 2 && gen_flush(wl) >= (s.kind == FXPQ_SRC_ADD ? 16 : 4);
   int gblocks = 240;
-  if (s.kind != FXPQ_SRC_F32 && !d_sse && wl >= 2 && wl <= 23 + (s.kind != FXPQ_SRC_ADD) && n <= per) gblocks = 1;
-  if (s.kind == FXPQ_SRC_ACC) {
+  if (s.kind != FXPQ_SRC_F32 && sums && wl <= 24 && n <= per) gblocks = 1;
+  if (s.kind == FXPQ_SRC_ACC && sums) {
     int a = s.channels, b = per;
     while (b) {
       const int t = a % b;

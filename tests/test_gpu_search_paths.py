@@ -263,3 +263,20 @@ def test_exact_pass_of_one_block(fx, h, orc, n, wl):
     fl, sg, _ = orc.fl_search_i64(w, 9, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
     assert search(fx, h, src, n, wl, FL_LO, FL_HI) == (wl, fl, sg, 0)
     assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("channels", [70, 1080])
+def test_every_error_of_cblock_values(fx, h, orc, channels):
+    """All candidates' errors (128-bit items, any number of blocks) where the
+    sums would take a grid of the channels' multiple."""
+    import torch
+    rows = 140_001 // channels
+    acc = values(channels, rows * channels, 24, True).astype(np.int32).reshape(rows, channels)
+    ep = fx.epilogue(channels, 9, fmt_dev(8, 5, 1))
+    for wl in (1, 6, 8, 26):
+        note("every error", channels, wl)
+        ofl, osign, osse = orc.fl_search_i64(np.ravel(acc).astype(np.int64), 14, wl, fx.SIGN_AUTO, FL_LO, FL_HI)
+        sse = torch.zeros(FL_HI - FL_LO + 1, dtype=torch.float64, device=DEV)
+        assert search(fx, h, fx.src_acc(dev(acc), ep), acc.size, wl, FL_LO, FL_HI, sse) == (wl, ofl, osign, 0)
+        assert np.allclose(sse.cpu().numpy(), osse, rtol=1e-9, atol=0)
+    assert fx.sync_status(h) == 0
