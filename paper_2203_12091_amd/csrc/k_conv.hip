@@ -155,6 +155,7 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
     ld.cols(a, a_off, n0, wave, lane);
     ld.rows(a, m0, wave, lane);
     constexpr int OPS = decltype(ld)::kOps;
+    static_assert(OPS < 2 * TM * TN, "every load and the walk's step come before an MFMA of the slab");
     constexpr int D = 2;                // slabs in flight (3: two blocks per CU instead of three, 30% slower)
     constexpr int ST = (BM + BN) * 64;  // bytes of a stage: rows, then columns
     __shared__ __attribute__((aligned(16))) int8_t stage[(D + 1) * ST];
@@ -482,7 +483,8 @@ __global__ __launch_bounds__(256, MINW) void k_qconv(ConvArgs a) {
 
 template <int BM, int BN, int TM, int TN, int MINW, int EPI>
 static void conv_dispatch_loader(int loader, dim3 grid, hipStream_t st, const ConvArgs& a) {
-  // (256 x 64 tiles take the staged loaders, the others the ring)
+  // (256 x 64 tiles take the staged loaders, the others the ring; 256 x 128 ones
+  // only C % 64 == 0)
   if constexpr (BN == 64) {
     if (loader == LD_FAST64) k_qconv<BM, BN, TM, TN, MINW, LD_FAST64, EPI><<<grid, 256, 0, st>>>(a);
     else if (loader == LD_GEN16) k_qconv<BM, BN, TM, TN, MINW, LD_GEN16, EPI><<<grid, 256, 0, st>>>(a);
@@ -490,6 +492,8 @@ static void conv_dispatch_loader(int loader, dim3 grid, hipStream_t st, const Co
       if (loader == LD_RGB8) k_qconv<BM, BN, TM, TN, MINW, LD_RGB8, EPI><<<grid, 256, 0, st>>>(a);
       else k_qconv<BM, BN, TM, TN, MINW, LD_RGB4, EPI><<<grid, 256, 0, st>>>(a);
     }
+  } else if constexpr (BM == 256) {
+    k_qconv<BM, BN, TM, TN, MINW, LD_DMA64, EPI><<<grid, 256, 0, st>>>(a);
   } else {
     if (loader == LD_DMA64) k_qconv<BM, BN, TM, TN, MINW, LD_DMA64, EPI><<<grid, 256, 0, st>>>(a);
     else k_qconv<BM, BN, TM, TN, MINW, LD_DMA16, EPI><<<grid, 256, 0, st>>>(a);

@@ -407,6 +407,7 @@ __global__ __launch_bounds__(256, 2) void k_cblock_pred(ConvArgs a) {
     // tile's stores are not counted, which only waits longer).
     constexpr int OPS = Load::kOps, STORES = TM * TN * 4;
     static_assert(D <= 3 && OPS * (D - 1) + D * STORES < 64, "vmcnt range");
+    static_assert(OPS < 2 * TM * TN, "every load and the walk's step come before an MFMA of the slab");
     int8_t* cur = stage;
     int s = 0;
     unsigned ends = 0;
