@@ -47,12 +47,14 @@ struct Scratch {
   struct PredJob* pred_jobs;     // [kMaxPredJobs]
   long long* pred_slots_i;       // [kMaxPredJobs][kWinSlots][kWinPart]
   double* pred_slots_f;          // [kMaxPredJobs][kWinSlots][kWinPartF]
-  // first-layer filters re-laid with every filter row padded to 8 taps
-  // (kRgbWBytes; nullptr: not available, the packed RGB loader runs)
+  // first-layer filters re-laid with every filter row padded to whole chunks of
+  // four taps (kRgbWBytes; nullptr: not available, the packed RGB loader runs)
   int8_t* rgb_w;
 };
 
-constexpr size_t kRgbWBytes = 1 << 16;
+// 4096 7x7 filters (predicted call of 11250 x 1580 outputs, 7x7, pixel by pixel 69
+// us, by chunks 46.5; 64 KB held 256).
+constexpr size_t kRgbWBytes = 1 << 20;
 
 // Pending decisions of predicted calls in deferred mode (at most this many
 // between two fxpq_predicted_decide calls).

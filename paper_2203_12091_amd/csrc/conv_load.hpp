@@ -631,7 +631,7 @@ dim3 conv_setup(const fxpq_conv_desc& d, const void* x, int x_type, const int8_t
 void split_setup(ConvArgs& a, int& loader, int& cfg, dim3& grid, int cus);
 // The padded RGB layout: re-lays the filters into the handle's buffer, filter
 // rows padded to whole 16-byte chunks of four taps, and switches to the loader
-// that reads four pixels at a time.
-void rgb8_setup(const Ctx& c, const fxpq_conv_desc& d, ConvArgs& a, int& loader);
+// that reads four pixels at a time.  plain: the contraction alone.
+void rgb8_setup(const Ctx& c, const fxpq_conv_desc& d, ConvArgs& a, int& loader, bool plain);
 
 }  // namespace fxpq

@@ -517,12 +517,16 @@ __global__ void k_rgb8_weights(const int8_t* w, int K, int R, int S, int wrow, i
 // stride 4 35.6 / 71.0 -> 29.9 / 43.6; 32 x 224 x 224, 3x3 84.9 / 112.5 -> 83.4 /
 // 96.8 (two chunks per filter row -> one); 256 x 224 x 224, 7x7 stride 2 204.5 /
 // 274.8 -> 194.2 / 263.9 (addresses from the image row instead of 64-bit products).
-void rgb8_setup(const Ctx& c, const fxpq_conv_desc& d, ConvArgs& a, int& loader) {
+// A plain call of less than four slabs (up to 5x5) stays pixel by pixel: the re-lay's
+// launch takes 2 us and its loads no less (by chunks -> pixel by pixel, 1600 x 688,
+// 3x3 13.9 -> 11.9; 401408 x 64, 3x3 29.8 -> 27.2, 5x5 33.3 -> 33.7, 7x7 35.6 -> 44.0;
+// but predicted 40.8 -> 54.5, 47.2 -> 62.7, 51.0 -> 79.5).
+void rgb8_setup(const Ctx& c, const fxpq_conv_desc& d, ConvArgs& a, int& loader, bool plain) {
   // (the loader's pixel indices within an image are 32-bit)
   if (loader != LD_RGB4 || d.w < 4 || (int64_t)d.h * d.w > INT_MAX || !c.sc.rgb_w) return;
   const int chunks = (d.s + 3) / 4;
   const int64_t wrow8 = ((int64_t)d.r * chunks * 16 + 63) / 64 * 64;
-  if (d.k * wrow8 > (int64_t)kRgbWBytes) return;
+  if (d.k * wrow8 > (int64_t)kRgbWBytes || (plain && wrow8 < 4 * BK)) return;
   const int64_t n = d.k * wrow8;
   k_rgb8_weights<<<(int)((n + 255) / 256), 256, 0, c.stream>>>(a.w, d.k, d.r, d.s, a.wrow, c.sc.rgb_w,
                                                                (int)wrow8, chunks);
@@ -709,7 +713,7 @@ hipError_t launch_conv(const Ctx& c, const fxpq_conv_desc& d, const void* x, int
   a.mm_ticket = ticket_for(c, nb);
   a.mm_out = d_minmax;
   bool timed = timer_begin(c, FXPQ_TIMER_QCONV);
-  rgb8_setup(c, d, a, loader);
+  rgb8_setup(c, d, a, loader, true);
   conv_run<EPI_ACC>(a, loader, cfg, grid, c.stream);
   timer_end(c, timed, 2.0 * (double)a.M * (double)d.k * (double)(d.r * d.s * d.c));
   if (a.want_mm && !a.mm_ticket) return launch_minmax_fin(c, a.mm_part, nb, d_minmax);

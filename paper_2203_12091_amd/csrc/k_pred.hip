@@ -566,7 +566,7 @@ hipError_t launch_conv_pred(const Ctx& c, const fxpq_conv_desc& d, const void* x
   a.y_type = FXPQ_C8;
   a.flags = c.sc.flags;
   bool timed = timer_begin(c, FXPQ_TIMER_CBLOCK_PRED);
-  rgb8_setup(c, d, a, loader);
+  rgb8_setup(c, d, a, loader, false);
   switch (loader) {
     case LD_SPLIT64: pred_run<64, 64, LD_SPLIT64>(c, a); break;
     case LD_SPLIT64G: pred_run<64, 64, LD_SPLIT64G>(c, a); break;

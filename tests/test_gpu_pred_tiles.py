@@ -30,7 +30,8 @@ CASES = [
     (3, 3, 50, 47, 64, 3, 1, 1, False, True),       # one chunk
     (2, 3, 33, 61, 36, 9, 1, 4, False, False),      # three chunks, ragged columns
     (1, 3, 64, 64, 24, 5, 1, 2, True, False),       # two
-    (2, 3, 40, 37, 128, 11, 1, 5, True, True),      # filters too large to re-lay: pixel by pixel
+    (2, 3, 40, 37, 128, 11, 1, 5, True, True),      # two column tiles
+    (1, 3, 22, 19, 1824, 11, 1, 5, True, True),     # filters too large to re-lay: pixel by pixel
     (5, 3, 37, 3, 64, 3, 1, 1, False, False),       # rows narrower than a chunk
 ]
 
