@@ -21,7 +21,9 @@ rocprofv3 FETCH_SIZE / WRITE_SIZE summary and is reported only while the
 kernel sources match the profiled ones.  The contraction alone, the window
 passes and per-layer rooflines are reported beside it.
 
-Prints ONE JSON line.  --gpus above 1 exits: this build runs on one GPU.
+Prints ONE JSON line (summary(): short enough to survive in the last 2000
+characters of a captured output); --details FILE writes every figure.  --gpus
+above 1 exits: this build runs on one GPU.
 """
 import argparse
 import hashlib
@@ -38,11 +40,13 @@ HBM_PEAK_GBS = 8000.0
 INT8_PEAK_TOPS = 5000.0
 # fp64 / int32 vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-ops/s
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
-# lane-ops per output value the predicted C-Block's epilogue must execute:
-# value (colsum restore, convert, Scale / bias fma, ReLU) 4; per window
-# candidate (scale, round, clamp, sum q^2, sum W q) 2 x 5; clipping bound 3;
-# sum W^2 1; min / max 2; code (convert, pack) 2
-PRED_OPS_PER_VALUE = 22
+# lane-ops per output value of the predicted C-Block's epilogue, as executed
+# (straight-line tile, non-negative values, codes of the second candidate; one
+# more for the first's): min / max 2; value (convert, Scale / bias fma, ReLU) 3;
+# sum W^2 1; first candidate (round, sum q^2, sum W q) 3; second (add and round,
+# clamp, convert, sum W q) 4, its sum q^2 from dot products of packed codes 1/4;
+# clipping bound 3; code packed and transposed 2
+PRED_OPS_PER_VALUE = 18.25
 BATCH, IMAGE = 256, 224
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cblock_predicted_resnet50_b256_traffic.md")
 WINDOW_SOURCES = ["k_pred.hip", "conv_load.hpp", "fls.hpp", "values.hpp", "common.hpp"]
@@ -59,6 +63,7 @@ def parse():
     ap.add_argument("--cpu-sample-batch", type=int, default=12)
     ap.add_argument("--no-configs", action="store_true",
                     help="skip the other workloads' figures (FC layer, AlexNet, VGG-16, ResNet-18)")
+    ap.add_argument("--details", metavar="FILE", help="also write every figure (per layer, per workload) as JSON")
     ap.add_argument("--mode", choices=["bench", "profile", "copy", "sweep", "qparams", "reduction",
                                        "wide", "steps"],
                     default="bench",
@@ -662,6 +667,29 @@ def sweep_figures(dev):
             "setup_seconds_untimed": round(setup, 2)}
 
 
+def summary(out):
+    """The figures of the printed line: the workload's, and one or two per step
+    and per other workload."""
+    pick = lambda d, *keys: {k: d[k] for k in keys if k in d}
+    s = dict(out)
+    s["roofline"] = pick(out["roofline"], "bound", "achieved", "peak", "unit", "frac", "traffic", "kernel",
+                         "launches", "avg_launch_ms", "ops_per_output_value", "ms_per_forward")
+    s["fl_search"] = pick(out["fl_search"], "frac", "launches", "ms_per_forward")
+    s["mfma"] = pick(out["mfma"], "kernel", "achieved", "unit", "peak", "frac", "ms_per_forward")
+    if "compute_bound_layers" in out["mfma"]:
+        s["mfma"]["compute_bound_layers"] = pick(out["mfma"]["compute_bound_layers"], "layers", "achieved", "frac")
+    s.pop("requant", None)
+    s.pop("predicted_cblock", None)
+    if "sweep" in out:
+        s["sweep"] = pick(out["sweep"], "layer_evaluations", "seconds", "layer_eval_images_per_s")
+    if "configs" in out:
+        s["configs"] = {k: pick(v, "us_per_call", "images_per_s", "ms_per_forward_cold")
+                        for k, v in out["configs"].items()}
+    if "cpu_baseline" in out:
+        s["cpu_baseline"] = pick(out["cpu_baseline"], "value", "unit", "cores", "kind", "sample")
+    return s
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -772,9 +800,9 @@ def main():
                    "timed_forwards_rerun": timed_misses},
         "roofline": {"bound": "alu", "achieved": round(pr_alu, 2), "peak": round(ALU_PEAK_TOPS, 2),
                      "unit": "TOP/s", "frac": round(pr_alu / ALU_PEAK_TOPS, 4), "traffic": traffic,
-                     "kernel": "k_cblock_pred: predicted C-Block (conv + epilogue + FL-search window + codes)",
+                     "kernel": "k_cblock_pred",
                      "launches": pr_n, "avg_launch_ms": round(pr_ms / max(pr_n, 1), 5),
-                     "algorithmic_ops_per_launch": round(PRED_OPS_PER_VALUE * pr_vals / max(pr_n, 1)),
+                     "ops_per_launch": round(PRED_OPS_PER_VALUE * pr_vals / max(pr_n, 1)),
                      "ops_per_output_value": PRED_OPS_PER_VALUE, "ms_per_forward": round(pr_ms, 3),
                      "int8_tops": round(pr_ops / (pr_ms * 1e-3) / 1e12, 1) if pr_ms else None},
         "fl_search_gbs": round(achieved, 1),
@@ -808,7 +836,10 @@ def main():
         out["cpu_baseline"] = cpu_baseline(args.cpu_sample_batch)
         if not args.no_configs:
             out["cpu_baseline"]["configs"] = cpu_configs()
-    print(json.dumps(out), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(summary(out)), flush=True)
 
 
 if __name__ == "__main__":
