@@ -172,10 +172,6 @@ __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, 
   WinSetup w;
   w.u = fls_uniform<KIND>(s, mm, wl, sign_req, fl_lo, fl_hi);
   const double qabs = fmax(w.u.qmax, -w.u.qmin);
-  w.b0 = imax(fl_lo, w.u.beta_nosat);
-  w.b1 = (w.b0 + kWindow - 1 < fl_hi) ? w.b0 + kWindow - 1 : fl_hi;
-  w.nc = w.b1 - w.b0 + 1;
-  w.bce = (w.b1 < fl_hi) ? w.b1 + 1 : w.b1;
   w.split = SPLIT;
   bool range = false;
   if constexpr (KIND == FXPQ_SRC_F32) {
@@ -187,10 +183,10 @@ __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, 
     // max and decides with this call's, and both have to choose the same wherever
     // they agree on the window.
     range = w.u.ok && ldexp(w.u.absmax, w.u.sigma) >= 0x1p62;  // the exact pass's error
-    w.u.sigma = w.b1 + 24;
+    const int b0 = imax(fl_lo, w.u.beta_nosat), b1 = b0 + kWindow - 1 < fl_hi ? b0 + kWindow - 1 : fl_hi;
+    w.u.sigma = b1 + 24;
     w.u.wscale = ldexp(1.0, w.u.sigma);
-    if (w.b0 == w.u.beta_nosat &&
-        ldexp((qabs + 1.0) * qabs * (double)per_thread, w.b1 - w.b0 + 24) < kTwo53)
+    if (b0 == w.u.beta_nosat && ldexp((qabs + 1.0) * qabs * (double)per_thread, b1 - b0 + 24) < kTwo53)
       w.split = 0;
   }
   const double wmax = w.u.absmax * w.u.wscale;
@@ -201,6 +197,10 @@ __device__ inline WinSetup win_setup(const SrcDev& s, const double* mm, int wl, 
   else if (KIND != FXPQ_SRC_F32 && wmax * qabs * (double)per_thread >= kTwo53 &&
            (!SPLIT || ldexp(w.u.absmax, imax(fl_hi - w.u.sv, 0)) >= 0x1p62))
     w.verdict = 2;
+  w.b0 = imax(fl_lo, w.u.beta_nosat);
+  w.b1 = (w.b0 + kWindow - 1 < fl_hi) ? w.b0 + kWindow - 1 : fl_hi;
+  w.nc = w.b1 - w.b0 + 1;
+  w.bce = (w.b1 < fl_hi) ? w.b1 + 1 : w.b1;
   return w;
 }
 

@@ -20,8 +20,10 @@
 //     error, the clipping error at the first of them (non-decreasing in fl),
 //     exceeds an upper bound of the window's best error.
 // Pass 2 ("general", only when pass 1 could not decide, when the caller asks
-//   for every error, or for word lengths above 16): the exact error of every
-//   remaining candidate in 128-bit integer arithmetic, compared exactly.
+//   for every error, or for word lengths of 1 or above 16): the remaining
+//   candidates by the same exact sums in fp64 with flushes to int64 (word lengths
+//   up to 25; W in two parts, or in three from 2^52 on), or by their exact errors
+//   in 128-bit integer arithmetic (every error asked for, longer words, 1 bit).
 #include <type_traits>
 
 #include "fls.hpp"
@@ -598,7 +600,9 @@ __device__ inline WinResult win_decide(const WinSetup& ws, int nce, int fl_hi,
     // Upper bound of the window's best error; the clipping error at fl is a
     // lower bound of the error of every candidate >= fl (it is non-decreasing
     // in fl), so the first bound above the best error excludes the rest
-    // (relative fp64 error of each sum, in any summation order, < 2^-40).
+    // (relative fp64 error of each sum < 2^-35: no negative terms, at most 2^16
+    // added one after the other in a thread of a predicted C-Block's 1024 tiles or
+    // of an eltwise pass, 2^10 blocks in a slot, some 2^-50 in a term).
     double v2 = f[0];
     double sse_ub = (v2 * (1.0 + 0x1p-30) + kd + fabs(kd) * 0x1p-50 + v2 * 0x1p-50);
     sse_ub = ldexp(sse_ub, -2 * u.sigma) * (1.0 + 0x1p-50);
@@ -1092,8 +1096,8 @@ __device__ void general_sums_decide(int wl, int sigma, const GenPlan& g,
 // Exact errors of the remaining candidates over (candidate, chunk) items; the
 // last block to finish sums the chunk partials and decides.  Nothing runs
 // unless the window pass left candidates undecided (and only then is the
-// device-scope release / acquire paid).
-template <int KIND, int DT>
+// device-scope release / acquire paid).  ONE: a single block runs it.
+template <int KIND, int DT, bool ONE = false>
 __device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, int fl_lo, int fl_hi,
                                             int nchunks, const double* mm, const GenPlan& gp,
                                             unsigned long long* part, unsigned* done,
@@ -1123,14 +1127,15 @@ __device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, 
   const long long qmin = sign ? -(1ll << (wl - 1)) : 0;
   // Word lengths 2..25: the candidates' exact sums in fp64 of W = v 2^(fl_hi + 24)
   // (fp32) or v, four per read of the values.  A block's sum q^2 has to fit 63
-  // bits.  Every block reduces every candidate's sums (3 us per four of the
-  // three-part ones): where the 128-bit errors' items, one per candidate and 65536
-  // values, spread over the blocks, few values go there (24 candidates of 12000
-  // fp32 values 57 against 72 us, of 100000 115 against 80).
+  // bits.  |W| from 2^52 on: three-part sums of int64 values and in one block; over
+  // many, where every block reduces every candidate's sums (3 us per four), the
+  // 128-bit errors' items spread better (24 candidates of 12000 fp32 values 57
+  // against 72 us), and the code alone slowed the searches that need neither (a
+  // C-Block's by 0.7 us).  (int32 values never get there.)
+  constexpr bool kParts3 = KIND == FXPQ_SRC_INT ? DT == FXPQ_I64 : ONE;
   const int sigf = (KIND == FXPQ_SRC_F32) ? sigma : sv;
   const bool parts3 = absmax * ldexp(1.0, sigf - sv) >= kTwo52;
-  if (wl >= 2 && gen_flush(wl) >= Pack<KIND, DT>::EP && !d_sse &&
-      (!parts3 || (KIND == FXPQ_SRC_INT && DT == FXPQ_I64) || gridDim.x == 1 || n >= 32768) &&
+  if (wl >= 2 && gen_flush(wl) >= Pack<KIND, DT>::EP && !d_sse && (kParts3 || !parts3) &&
       ldexp((double)(n / gridDim.x + kThreads * Pack<KIND, DT>::EP * kWinSets), 2 * wl) < 0x1p62) {
     const FlsU u = fls_uniform<KIND>(s, mm, wl, sign, fl_lo, fl_hi);
     // candidates below beta_nosat never win (see the top of this file); int64
@@ -1138,8 +1143,12 @@ __device__ __forceinline__ void general_run(const SrcDev& s, int64_t n, int wl, 
     const int nosat = u.beta_nosat - (KIND == FXPQ_SRC_INT && DT == FXPQ_I64 && absmax >= kTwo53 ? 1 : 0);
     const int lo = extra == INT_MIN ? imax(glo, nosat < ghi ? nosat : ghi) : glo;
     const GenPlan gf{1, 0, sign, lo, ghi, extra};
-    if (parts3) general_sums_wide<KIND, DT>(s, n, wl, u, gf, part);
-    else general_sums<KIND, DT>(s, n, wl, u, gf, part);
+    bool wide = false;
+    if constexpr (kParts3) {
+      wide = parts3;
+      if (wide) general_sums_wide<KIND, DT>(s, n, wl, u, gf, part);
+    }
+    if (!wide) general_sums<KIND, DT>(s, n, wl, u, gf, part);
     __threadfence();
     __syncthreads();
     if (threadIdx.x == 0) last = atomicAdd(done, 1u) == gridDim.x - 1;
@@ -1340,7 +1349,7 @@ __global__ __launch_bounds__(kThreads) void k_search_small(
     __syncthreads();
     const GenPlan gp = gp_sh;
     if (!gp.need || gp.status) return;
-    general_run<KIND, DT>(s, n, wl, fl_lo, fl_hi, 1, mm, gp, part, done, out, nullptr, flags);
+    general_run<KIND, DT, true>(s, n, wl, fl_lo, fl_hi, 1, mm, gp, part, done, out, nullptr, flags);
   }
 }
 
@@ -1423,16 +1432,17 @@ static hipError_t general_pass(const Ctx& c, const SrcDev& s, int64_t n, int wl,
   int nchunks = (int)((n + 65535) / 65536);
   if (nchunks > kGenChunks) nchunks = kGenChunks;
   if (nchunks < 1) nchunks = 1;
-  // about a block per CU.  Where the pass forms sums: one block where it alone has
-  // values (every block reduces every candidate's sums: 256 int32 values at 17 bits
-  // 34 -> 18 us, with an outlier 49 -> 33); for C-Block values the grid stride is a
+  // about a block per CU.  Where the pass forms sums: 24 blocks while they have a
+  // value per thread and load (every block reduces every candidate's sums, and its
+  // fences cost: 256 int32 values at 17 bits 34 -> 19 us, with an outlier 49 -> 33;
+  // 12000 int64 values 34 -> 20, 49 -> 35); for C-Block values the grid stride is a
   // multiple of the channels where at most kGenChunks blocks allow it (the 128-bit
   // errors take whatever blocks there are: every error of 500000 values in 135
   // blocks 310 us, in 240 177).
   const int per = kThreads * 4;  // values per block and iteration
   const bool sums = !d_sse && wl >= 2 && gen_flush(wl) >= (s.kind == FXPQ_SRC_ADD ? 16 : 4);
   int gblocks = 240;
-  if (s.kind != FXPQ_SRC_F32 && sums && wl <= 24 && n <= per) gblocks = 1;
+  if (sums && wl <= 24 && n <= 24 * per) gblocks = 24;
   if (s.kind == FXPQ_SRC_ACC && sums) {
     int a = s.channels, b = per;
     while (b) {

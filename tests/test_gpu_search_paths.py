@@ -231,17 +231,16 @@ def test_integer_search_of_53_bits(fx, h, orc, n, wl):
     assert fx.sync_status(h) == 0
 
 
-@pytest.mark.parametrize("n", [1, 16, 256, 1023, 1024, 1025])
+@pytest.mark.parametrize("n", [1, 16, 1023, 1025, 24_576, 24_577])
 @pytest.mark.parametrize("wl", [17, 20, 23, 24, 25])
-def test_exact_pass_of_one_block(fx, h, orc, n, wl):
-    """Word lengths past the window's, up to the values of one block and one more
-    (there the exact pass is one block): every source but fp32, which is there
-    to compare."""
+def test_exact_pass_of_few_blocks(fx, h, orc, n, wl):
+    """Word lengths past the window's, up to the values of 24 blocks (the exact
+    pass takes that few) and one more: every source."""
     import torch
-    g = synth.rng_for(n + wl, "one-block")
+    g = synth.rng_for(n + wl, "few-blocks")
     v = values(n * wl, n, 24, True)
     sd = torch.tensor([9], dtype=torch.int32, device=DEV)
-    note("one block", n, wl)
+    note("few blocks", n, wl)
     want = (wl, *orc.fl_search_i64(v, 9, wl, fx.SIGN_AUTO, FL_LO, FL_HI)[:2], 0)
     assert search(fx, h, fx.src_int(dev(v.astype(np.int32)), fx.I32, sd), n, wl, FL_LO, FL_HI) == want
     assert search(fx, h, fx.src_int(dev(v), fx.I64, sd), n, wl, FL_LO, FL_HI) == want
