@@ -496,20 +496,18 @@ __device__ inline void win_write_partials(const WinAcc& acc, int nb, int64_t bid
 }
 
 // Block results of a window pass over integer values (no W split: PH is
-// zero).  Fewer reductions than win_write_partials: sum q^2 per candidate is
-// reduced in fp64, where it is exact (below 2^53 for word lengths up to 16
-// and at most 2^17 values per block); sum W q as the 32-bit halves of the
-// thread's exact int64 sum wq (below 2^62); the bound sums in fp64.  Same
-// slot contents.
+// zero).  Fewer reductions than win_write_partials: sum q^2 per candidate (below
+// 2^53 per thread) is reduced whole in int64, exact while the wave's stays below
+// 2^63; sum W q as the 32-bit halves of the thread's exact int64 sum wq (below
+// 2^62); the bound sums in fp64.  Same slot contents.
 __device__ inline void win_write_partials_wq(const WinAcc& acc, const long long* wq, int nb,
                                              int64_t bid, long long* part_i, double* part_f,
                                              WinShared& sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double a[kWindow];
-  long long ph[kWindow], pl[kWindow];
+  long long a[kWindow], ph[kWindow], pl[kWindow];
 #pragma unroll
   for (int j = 0; j < kWindow; ++j) {
-    a[j] = wave_reduce(acc.A[j], OpAddD());
+    a[j] = wave_reduce(exact_i64(acc.A[j]), OpAddL());
     ph[j] = wave_reduce(wq[j] >> 32, OpAddL());
     pl[j] = wave_reduce(wq[j] & 0xFFFFFFFFll, OpAddL());
   }
@@ -520,9 +518,8 @@ __device__ inline void win_write_partials_wq(const WinAcc& acc, const long long*
   if (lane == 0) {
 #pragma unroll
     for (int j = 0; j < kWindow; ++j) {
-      const long long aj = exact_i64(a[j]);
-      sh.i[w][6 * j + 0] = aj >> 32;
-      sh.i[w][6 * j + 1] = aj & 0xFFFFFFFFll;
+      sh.i[w][6 * j + 0] = a[j] >> 32;
+      sh.i[w][6 * j + 1] = a[j] & 0xFFFFFFFFll;
       sh.i[w][6 * j + 2] = 0;  // W q summed unsplit: the high part is zero
       sh.i[w][6 * j + 3] = 0;
       sh.i[w][6 * j + 4] = ph[j];
