@@ -6,8 +6,8 @@ and the last one is partial."""
 import numpy as np
 import pytest
 
-from gpu_util import DEV, fmt_dev, fmt_host, host, note
-from test_gpu_cblock import Case
+from gpu_util import DEV, empty, fmt_dev, fmt_host, host, note, predicted_outcome
+from test_gpu_cblock import FL_HI, FL_LO, Case
 
 pytestmark = pytest.mark.gpu
 
@@ -59,6 +59,12 @@ def test_predicted_many_tiles(fx, h, case):
     import torch
     c = Case(*case, seed=91 + CASES.index(case)).upload(fx, h)
     hits = 0
+    # the C-Block's values (scale 29) from the contraction's accumulators
+    acc = empty((c.n // c.K, c.K), torch.int32)
+    fx.qconv(h, c.desc, c.xd, c.x_type, c.wd, c.colsum, c.ep, acc)
+    assert (c.fl_in + c.fl_w, c.fl_b, c.fl_a1, c.fl_a2) == (14, 11, 15, 15)
+    v = (acc.long() + c.bd.long() * 8) * c.a1d.long() + c.a2d.long() * 2 ** 14
+    v = (v.clamp(min=0) if c.relu else v).double()
     for wl in (8, 6, 5, 4):
         note("predicted tiles", case, wl)
         fmt, codes, exact = c.unfused(fx, h, wl)
@@ -72,7 +78,9 @@ def test_predicted_many_tiles(fx, h, case):
             out = fmt_dev(wl, fmt[1], fmt[2])
             y = c.predicted(fx, h, wl, mm, out, miss)
             assert np.array_equal(host(mm), exact)
-            if int(host(miss)[0]) == 0:
+            m, want = int(host(miss)[0]), predicted_outcome(v, 29, wl, fmt[2], FL_LO, FL_HI)
+            assert m == want or (want is None and m != 1)
+            if m == 0:
                 hits += 1
                 assert fmt_host(out) == fmt
                 assert np.array_equal(host(y), codes)

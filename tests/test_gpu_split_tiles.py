@@ -5,7 +5,7 @@ oracle (codes, format, min / max are exact)."""
 import numpy as np
 import pytest
 
-from gpu_util import DEV, fmt_dev, fmt_host, host, note
+from gpu_util import DEV, dev, fmt_dev, fmt_host, host, note, predicted_outcome
 from test_gpu_cblock import FL_HI, FL_LO, Case, decode8
 
 pytestmark = pytest.mark.gpu
@@ -63,6 +63,8 @@ def test_split_tiles(fx, h, orc, case):
     c = Case(*case, seed=131 + CASES.index(case)).upload(fx, h)
     v, s = c.oracle_values(orc)
     exact = (float(v.min()), float(v.max()))
+    vd = dev(v).double()
+    hits = 0
     for wl in (8, 4):
         note("split tiles", case, wl)
         ofl, osg, _ = orc.fl_search_i64(v, s, wl, orc.SIGN_AUTO, FL_LO, FL_HI)
@@ -76,9 +78,15 @@ def test_split_tiles(fx, h, orc, case):
             out = fmt_dev(wl, ofl, osg)
             y = c.predicted(fx, h, wl, mmd, out, miss)
             assert tuple(host(mmd)) == exact
-            if lo == lo and int(host(miss)[0]) == 0:
+            m = int(host(miss)[0])
+            if lo != lo:
+                assert m == 1
+                continue
+            want = predicted_outcome(vd, s, wl, osg, FL_LO, FL_HI)
+            assert m == want or (want is None and m != 1)
+            if m == 0:
+                hits += 1
                 assert fmt_host(out) == (wl, ofl, osg, 0)
                 assert np.array_equal(decode8(host(y), osg == 0), codes)
-            elif lo != lo:
-                assert int(host(miss)[0]) == 1
+    assert hits
     assert fx.sync_status(h) == 0
