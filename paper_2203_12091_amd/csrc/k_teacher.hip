@@ -317,14 +317,15 @@ static int elem_grid(int64_t n) {
 // Outputs that one thread each computes faster than 32 x 32 tiles: few and
 // shallow ones (a tile takes its 32 channels and 32 of depth whatever exists of
 // them), and up to eight channels of a few input channels.  us, per output / in
-// tiles, pixels x channels, depth: 784 x 64, 1 5.1 / 6.4; 12544 x 16, 9 5.2 / 7.2;
+// tiles, pixels x channels, depth: 784 x 64, 1 5.1 / 6.4; 12544 x 16, 9 5.2 / 7.2, x 64
+// 10 / 10; 6240 x 269, 4 9.0 / 10.9; 100352 x 16, 4 9.1 / 11.8, x 24 12 / 12;
 // 802816 x 4, 4 15 / 61, x 16 52 / 63, x 24 75 / 64; 802816 x 1, 9 10 / 77, x 8 57 /
 // 79, x 12 84 / 80; 802816 x 8, 147 (3 input channels) 374 / 439, 100352 x 4 31 / 69,
 // x 12 67 / 69, but 784 x 4 17 / 11; 16 input channels, 100352 x 4, 144 25 / 50, x 8
 // 37 / 51, x 2 66 / 56, x 6 144 / 57; 64, x 4, 576 218 / 185.
 static bool narrow_teacher(int64_t M, int K, int C, int64_t depth) {
   const int64_t one = K * (depth + 3);  // about a pixel's work
-  if (one <= (C <= 4 ? 128 : 64) || (depth <= 16 && M * one <= 2500000)) return true;
+  if (one <= (C <= 4 ? 128 : 64) || (depth <= 16 && M * one <= (depth <= 9 ? 12000000 : 2500000))) return true;
   if (K > 8) return false;
   if (C <= 4) return depth <= 32 || M >= 65536;
   return C <= 16 && M >= 65536 && (K == 1 || K % 4 == 0);
