@@ -1437,8 +1437,8 @@ static hipError_t general_pass(const Ctx& c, const SrcDev& s, int64_t n, int wl,
   // fences cost: 256 int32 values at 17 bits 34 -> 19 us, with an outlier 49 -> 33;
   // 12000 int64 values 34 -> 20, 49 -> 35); for C-Block values the grid stride is a
   // multiple of the channels where at most kGenChunks blocks allow it (the 128-bit
-  // errors take whatever blocks there are: every error of 500000 values in 135
-  // blocks 310 us, in 240 177).
+  // errors take whatever blocks there are: every error of 622080 values in 135
+  // blocks 321 us, in 240 176).
   const int per = kThreads * 4;  // values per block and iteration
   const bool sums = !d_sse && wl >= 2 && gen_flush(wl) >= (s.kind == FXPQ_SRC_ADD ? 16 : 4);
   int gblocks = 240;
