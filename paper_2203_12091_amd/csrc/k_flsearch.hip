@@ -134,8 +134,9 @@ __device__ inline void win_loop(const SrcDev& s, int64_t n, const FlsU& u, const
     *mx = hi;
   }
 }
-// The variant of the min / max and of the split, then the block's partial sums.
-template <int KIND, int DT, int NB, bool CODES, bool MM = false>
+// The variant of the min / max and of the split (ANY: ws.split decides for every
+// source), then the block's partial sums.
+template <int KIND, int DT, int NB, bool CODES, bool MM = false, bool ANY = KIND == FXPQ_SRC_F32>
 __device__ __forceinline__ void win_pass(const SrcDev& s, int64_t n, const WinSetup& ws,
                                          const double* mm, const WinCodes& wcd, int64_t bid,
                                          long long* part_i, double* part_f, WinShared& wsh,
@@ -153,7 +154,7 @@ __device__ __forceinline__ void win_pass(const SrcDev& s, int64_t n, const WinSe
     if constexpr (SP) win_write_partials(acc, NB, bid, part_i, part_f, wsh);
     else win_write_partials_int(acc, NB, bid, part_i, part_f, wsh);
   };
-  if constexpr (KIND == FXPQ_SRC_F32) {
+  if constexpr (ANY) {
     if (ws.split) run(std::true_type());
     else run(std::false_type());
   } else if constexpr (win_split(KIND, DT)) {
@@ -1326,8 +1327,17 @@ __global__ __launch_bounds__(kThreads) void k_search_small(
   }
   __syncthreads();
   constexpr int NB = kCeBounds;
-  const WinSetup ws = win_setup<KIND, win_split(KIND, DT)>(s, mm, wl, sign_req, fl_lo, fl_hi,
-                                                           MODE_SEARCH, per_thread);
+  // Integer sums past the unsplit bound go to the exact pass, which refuses values
+  // that the window would take; the streaming pass over so few values adds at most
+  // 2 V of them per thread.  Its bound decides here too, and sums that this block's
+  // longer ones take past 2^53 are split (int32 values never are).
+  constexpr bool kInt = KIND != FXPQ_SRC_F32;
+  constexpr bool kAny = !win_split(KIND, DT) && KIND != FXPQ_SRC_INT;
+  constexpr int V4 = KIND == FXPQ_SRC_ADD ? 16 : 4;
+  WinSetup ws = win_setup<KIND, win_split(KIND, DT)>(s, mm, wl, sign_req, fl_lo, fl_hi, MODE_SEARCH,
+                                                     kInt ? (n < V4 ? V4 : 2 * V4) : per_thread);
+  if constexpr (kAny)
+    ws.split = ws.u.absmax * ws.u.wscale * fmax(ws.u.qmax, -ws.u.qmin) * (double)per_thread >= kTwo53;
   if (ws.verdict != 0) {
     if (threadIdx.x == 0) {
       win_verdict_write(ws, wl, fl_lo, fl_hi, plan, out, flags);
@@ -1335,7 +1345,7 @@ __global__ __launch_bounds__(kThreads) void k_search_small(
                       plan->gen_extra};
     }
   } else {
-    win_pass<KIND, DT, NB, false>(s, n, ws, mm, WinCodes{}, 0, slot_i, slot_f, wsh);
+    win_pass<KIND, DT, NB, false, false, !kInt || kAny>(s, n, ws, mm, WinCodes{}, 0, slot_i, slot_f, wsh);
     __syncthreads();
     if (threadIdx.x < 64) {
       const WinResult r = win_decide(ws, NB, fl_hi, slot_i, slot_f);

@@ -158,9 +158,9 @@ def test_int64_extreme_rounded_to_the_bound(fx, h, orc, n, wl):
     assert fx.sync_status(h) == 0
 
 
-def search(fx, h, src, n, wl, lo, hi, sse=None):
+def search(fx, h, src, n, wl, lo, hi, sse=None, sign=None):
     out = fmt_new()
-    fx.fl_search(h, src, n, wl, fx.SIGN_AUTO, lo, hi, out, sse)
+    fx.fl_search(h, src, n, wl, fx.SIGN_AUTO if sign is None else sign, lo, hi, out, sse)
     return fmt_host(out)
 
 
@@ -278,4 +278,37 @@ def test_every_error_of_cblock_values(fx, h, orc, channels):
         sse = torch.zeros(FL_HI - FL_LO + 1, dtype=torch.float64, device=DEV)
         assert search(fx, h, fx.src_acc(dev(acc), ep), acc.size, wl, FL_LO, FL_HI, sse) == (wl, ofl, osign, 0)
         assert np.allclose(sse.cpu().numpy(), osse, rtol=1e-9, atol=0)
+    assert fx.sync_status(h) == 0
+
+
+@pytest.mark.parametrize("n", [1, 15, 300, 2049, 4096, 8192, 9000])
+def test_integer_search_beyond_the_exact_pass(fx, h, orc, n):
+    """Values that the window decides although the exact pass would refuse them
+    (|v| 2^(fl_hi - scale) of 2^62 and more): whatever number of values a thread
+    adds, the same are taken.  The best fl lies in the range's lower part, so the
+    oracle's search up to fl 29 finds it."""
+    import torch
+    g = synth.rng_for(n, "beyond")
+    for wl, bits in ((8, 41), (8, 42), (16, 33), (16, 34)):  # |W| max |q| 8 below 2^53
+        s = 9
+        v = np.clip(g.standard_normal(n) * 2.0 ** (bits - 3), -2 ** bits * 0.95, 2 ** bits * 0.95).astype(np.int64)
+        v[n // 2] = int(2 ** bits * 0.96)
+        v[n // 3] = -int(2 ** bits * 0.95)
+        note("beyond", n, wl, bits)
+        fl, sg, _ = orc.fl_search_i64(v, s, wl, 1, -64, 24 if bits > 40 else 32)
+        sd = torch.tensor([s], dtype=torch.int32, device=DEV)
+        assert search(fx, h, fx.src_int(dev(v), fx.I64, sd), n, wl, -64, 50, sign=1) == (wl, fl, sg, 0)
+        # C-Block values acc * a1 of the same size
+        a1 = np.array([2 ** 22 - 3], np.int32)
+        acc = (v >> 22).astype(np.int32)
+        ep = fx.epilogue(1, 3, fmt_dev(8, 2, 1), scale=dev(a1), fl_scale=4)
+        w = acc.astype(np.int64) * int(a1[0])
+        fl, sg, _ = orc.fl_search_i64(w, s, wl, 1, -64, 24 if bits > 40 else 32)
+        assert search(fx, h, fx.src_acc(dev(acc.reshape(-1, 1)), ep), n, wl, -64, 50, sign=1) == (wl, fl, sg, 0)
+    a, b = g.integers(0, 256, n), g.integers(-128, 128, n)
+    a[n // 2] = 255
+    src = fx.src_add(dev((a - 128).astype(np.int8)), fx.C8, fmt_dev(8, 0, 0), dev(b.astype(np.int8)), fx.C8,
+                     fmt_dev(8, 33, 1), False)
+    fl, sg, _ = orc.fl_search_i64((a.astype(np.int64) << 33) + b, 33, 8, 1, -20, 50)
+    assert search(fx, h, src, n, 8, -20, 64, sign=1) == (8, fl, sg, 0)
     assert fx.sync_status(h) == 0
